@@ -49,7 +49,10 @@ struct GatherProgram {
     float* w;
 };
 
-constexpr float kDftScale = 16.0f;   // of the split FP16 DFT operand (kernels_pair.hip)
+// of the split FP16 DFT operand (kernels_pair.hip)
+constexpr int kDftScaleLog2 = 4;
+constexpr float kDftScale = 1 << kDftScaleLog2;
+constexpr int kRowBounds = 16;   // bounds per channel and pol: of four window rows each
 
 // Operand types of the GEMM-gridding form (gridding on the matrix cores).
 constexpr int kBgFp16 = 0, kBgFp8 = 1;
@@ -105,7 +108,13 @@ struct SubDev {
     uint8_t* pair_tap = nullptr;
     float* pair_w = nullptr;
     void* pair_dft = nullptr;         // FP16 DFT operand
-    float* gmag = nullptr;            // [C][slices][P] largest weight sum of a slice's cells (FP32 form)
+    // scales of its FP32 form
+    float* row_bound = nullptr;       // [C][kRowBounds][P] bounds of |Re G| + |Im G| summed over a window row
+    float* peak = nullptr;            // [C][A][P] largest |weight| of an antenna
+    int32_t* row_top = nullptr;       // [C] most entries of a window row
+    float* range = nullptr;           // [2][C][kRowBounds][P] the same by a call's samples too (accumulate, noalloc)
+    int32_t* uneven = nullptr;        // [2][C] 1: the channel's weights are uneven
+    int use_range = 0;                // per call: the samples are looked through for that bound
     // gridding on the matrix cores (EPIC_GRID_DENSE_GEMM / EPIC_GRID_BLOCK_GEMM)
     int gridder = EPIC_GRID_GATHER;   // gridding form this sub-array's kernel runs
     int R4max = 0;                    // largest window row count, rounded up to 4
@@ -169,6 +178,14 @@ hipError_t launch_gaussian_taps(const SubDev& d, double sigma, hipStream_t st);
 hipError_t launch_twiddles(const SubDev& d, hipStream_t st);
 // the weights of the gather programs the plan holds
 hipError_t launch_weights(const SubDev& d, hipStream_t st);
+
+// The bounds that a call's samples give (d.range), for channels whose antennas'
+// weights differ by kPairSpread or more; the weights' bounds for the others.
+// Below that spread the weights' bounds do by themselves: 255 of 256 antennas
+// silent and 15 times the live one's weight, samples of +-1, leave 0.7e-6 on 18 x
+// 18 cells (1.4e-7 by the samples).  Ordinary gains do not pay for the look.
+constexpr float kPairSpread = 16.0f;
+hipError_t launch_range(const SubDev& d, const uint8_t* samples, int64_t n_time, hipStream_t st);
 
 // The FP32 hot path for one sub-array: n_time spectra of uint8 [T][C][A][P].
 // fp32_configure picks the launch shape; with device < 0 it makes no HIP call.

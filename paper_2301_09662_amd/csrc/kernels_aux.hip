@@ -79,22 +79,38 @@ __device__ __forceinline__ void put_weight(float* __restrict__ w, int64_t e, int
     }
 }
 
+// |w_re| + |w_im| of an antenna's tap: the most it makes of a component of size 1.
+__device__ __forceinline__ float weight_size(const float* __restrict__ taps, const float* __restrict__ gains,
+                                             int64_t cap, int kk, int tap) {
+    const float2 t = reinterpret_cast<const float2*>(taps)[cap * kk + tap];
+    float2 g = make_float2(1.f, 0.f);
+    if (gains) g = reinterpret_cast<const float2*>(gains)[cap];
+    return fabsf(g.x * t.x - g.y * t.y) + fabsf(g.x * t.y + g.y * t.x);
+}
+
 // Weights of the gather programs (the plain one and the sliced one, either may
 // be absent) in one launch: blockIdx.y is the channel, blockIdx.x counts the
 // blocks of the plain program (an entry per thread), then of the sliced one (a
-// slice per block: lanes take its cells, the four waves its groups in turn).  Layout per entry by weight mode:
+// slice per block: lanes take its cells, the four waves its groups in turn),
+// then, for the scales of the FP32 form, of the window's rows (a wave sums the
+// weights of a row's entries, a block takes the largest of four rows: a sample's
+// two components are at most eight, so 16 times the sum bounds the row's
+// |Re G| + |Im G|) and of the antennas (eight lanes take the largest of an
+// antenna's and pol's).  Layout per entry by weight mode:
 // complex -> 2P floats (re, im per pol); real -> P floats (re per pol); shared
-// -> 1 float (the X weight, equal to Y).  For the FP32 form mag[c][slice][pol]
-// receives the largest sum of |w_re| + |w_im| over a cell's entries.
+// -> 1 float (the X weight, equal to Y).
 template <int P, int wm>
 __global__ void __launch_bounds__(256) weights_kernel(GatherProgram plain, int nb_plain, GatherProgram sliced,
-                                                      const float* __restrict__ taps, const float* __restrict__ gains,
-                                                      int A, int K, float* __restrict__ mag, int n_slice) {
-    const int c = blockIdx.y;
+                                                      int nb_sliced, const float* __restrict__ taps,
+                                                      const float* __restrict__ gains,
+                                                      const int32_t* __restrict__ cells, int A, int K,
+                                                      float* __restrict__ row_bound, float* __restrict__ peak) {
+    const int c = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     constexpr int np = wm == kWShared ? 1 : P;
-    if ((int)blockIdx.x < nb_plain) {
+    int b = blockIdx.x;
+    if (b < nb_plain) {
         const ChanInfo ci = plain.chans[c];
-        const int e = blockIdx.x * 256 + threadIdx.x;
+        const int e = b * 256 + threadIdx.x;
         if (e >= ci.n_grp * kGroup) return;
         const int64_t ge = (int64_t)ci.grp_off * kGroup + e;
         const int a = plain.ant[ge], tap = plain.tap[ge];
@@ -105,44 +121,151 @@ __global__ void __launch_bounds__(256) weights_kernel(GatherProgram plain, int n
         }
         return;
     }
+    b -= nb_plain;
     const ChanInfo ci = sliced.chans[c];
-    const int slice = blockIdx.x - nb_plain, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (64 * slice >= ci.n_cell) return;
-    const CellDesc d = sliced.desc[ci.cell_off + 64 * slice + lane];
-    float s[2] = {0.f, 0.f};
-    for (int j = wv; j < (int)(d.x >> 16); j += 4) {
-        // a group's indices, then all its taps and gains: two round trips
-        const int64_t ge = ((int64_t)ci.grp_off + d.y + 64 * j + lane) * kGroup;
-        const ushort4 an = *reinterpret_cast<const ushort4*>(sliced.ant + ge);
-        const uchar4 tp = *reinterpret_cast<const uchar4*>(sliced.tap + ge);
-        const int aa[4] = {an.x, an.y, an.z, an.w}, tt[4] = {tp.x, tp.y, tp.z, tp.w};
-        double wr[np][kGroup], wi[np][kGroup];
+    if (b < nb_sliced) {
+        if (64 * b >= ci.n_cell) return;
+        const CellDesc d = sliced.desc[ci.cell_off + 64 * b + lane];
+        for (int j = wv; j < (int)(d.x >> 16); j += 4) {
+            // a group's indices, then all its taps and gains: two round trips
+            const int64_t ge = ((int64_t)ci.grp_off + d.y + 64 * j + lane) * kGroup;
+            const ushort4 an = *reinterpret_cast<const ushort4*>(sliced.ant + ge);
+            const uchar4 tp = *reinterpret_cast<const uchar4*>(sliced.tap + ge);
+            const int aa[4] = {an.x, an.y, an.z, an.w}, tt[4] = {tp.x, tp.y, tp.z, tp.w};
+            double wr[np][kGroup], wi[np][kGroup];
 #pragma unroll
-        for (int q = 0; q < kGroup; ++q)
+            for (int q = 0; q < kGroup; ++q)
 #pragma unroll
-            for (int p = 0; p < np; ++p)   // padding: any tap's loads, so that no branch parts them
-                entry_weight(taps, gains, c, A, P, K, aa[q], tt[q] == 255 ? 0 : tt[q], p, &wr[p][q], &wi[p][q]);
+                for (int p = 0; p < np; ++p)   // padding: any tap's loads, so that no branch parts them
+                    entry_weight(taps, gains, c, A, P, K, aa[q], tt[q] == 255 ? 0 : tt[q], p, &wr[p][q], &wi[p][q]);
 #pragma unroll
-        for (int q = 0; q < kGroup; ++q)
+            for (int q = 0; q < kGroup; ++q)
 #pragma unroll
-            for (int p = 0; p < np; ++p) {
-                const bool on = tt[q] != 255;
-                const double r = on ? wr[p][q] : 0.0, i = on ? wi[p][q] : 0.0;
-                put_weight(sliced.w, ge + q, wm, P, p, r, i);
-                s[p] += fabsf((float)r) + (wm == kWComplex ? fabsf((float)i) : 0.f);
-            }
+                for (int p = 0; p < np; ++p) {
+                    const bool on = tt[q] != 255;
+                    put_weight(sliced.w, ge + q, wm, P, p, on ? wr[p][q] : 0.0, on ? wi[p][q] : 0.0);
+                }
+        }
+        return;
     }
-    if (!mag) return;
-    if (wm == kWShared) s[1] = s[0];
-    __shared__ float sum[4][64][2];
-    sum[wv][lane][0] = s[0];
-    sum[wv][lane][1] = s[1];
+    b -= nb_sliced;
+    if (b < kRowBounds) {
+        __shared__ float red[4][2];
+        const int row = 4 * b + wv;
+        float s[2] = {0.f, 0.f};
+        for (int k = lane; row < ci.R && k < A * K; k += 64) {   // an antenna's taps in neighbouring lanes
+            const int a = k / K, dx = k - a * K;
+            const int64_t ca = (int64_t)c * A + a;
+            const int dy = ci.y0 + row - (cells[ca * 2 + 1] - K / 2);
+            if (dy < 0 || dy >= K) continue;
+#pragma unroll
+            for (int p = 0; p < P; ++p) s[p] += weight_size(taps, gains, ca * P + p, K * K, dy * K + dx);
+        }
+        for (int m = 32; m > 0; m >>= 1)
+            for (int p = 0; p < P; ++p) s[p] += __shfl_xor(s[p], m);
+        if (lane == 0)
+            for (int p = 0; p < P; ++p) red[wv][p] = s[p];
+        __syncthreads();
+        const int p = threadIdx.x;
+        if (p < P)
+            row_bound[((int64_t)c * kRowBounds + b) * P + p] =
+                16.0f * fmaxf(fmaxf(red[0][p], red[1][p]), fmaxf(red[2][p], red[3][p]));
+        return;
+    }
+    const int k = (b - kRowBounds) * 32 + threadIdx.x / 8;
+    if (k >= A * P) return;
+    const int64_t cap = (int64_t)c * A * P + k;
+    float w = 0.f;
+    for (int tap = threadIdx.x & 7; tap < K * K; tap += 8) w = fmaxf(w, weight_size(taps, gains, cap, K * K, tap));
+    for (int m = 4; m > 0; m >>= 1) w = fmaxf(w, __shfl_xor(w, m));
+    if ((threadIdx.x & 7) == 0) peak[cap] = w;
+}
+
+// ---- the range of the gridded values (FP32 form) --------------------------
+// One block per channel: clears its bound and says whether the antennas of a pol
+// (those that weigh anything) differ by kPairSpread or more.
+template <int P>
+__global__ void __launch_bounds__(256) range_start_kernel(const float* __restrict__ peak, int A,
+                                                          float* __restrict__ range, int32_t* __restrict__ uneven) {
+    __shared__ float red[2][4][2];
+    const int c = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    float hi = 0.f, lo = __builtin_huge_valf();   // of the thread's pol: the block's size is even
+    for (int k = threadIdx.x; k < A * P; k += 256) {
+        const float w = peak[(int64_t)c * A * P + k];
+        if (w > 0.f) {
+            hi = fmaxf(hi, w);
+            lo = fminf(lo, w);
+        }
+    }
+    for (int m = 32; m >= P; m >>= 1) {
+        hi = fmaxf(hi, __shfl_xor(hi, m));
+        lo = fminf(lo, __shfl_xor(lo, m));
+    }
+    if (lane < P) {
+        red[lane][wv][0] = hi;
+        red[lane][wv][1] = lo;
+    }
     __syncthreads();
-    if (wv < P) {   // wave p: the largest cell sum of pol p
-        float v = (sum[0][lane][wv] + sum[1][lane][wv]) + (sum[2][lane][wv] + sum[3][lane][wv]);
-        for (int m = 32; m > 0; m >>= 1) v = fmaxf(v, __shfl_xor(v, m));
-        if (lane == 0) mag[((int64_t)c * n_slice + slice) * P + wv] = v;
+    if (threadIdx.x < P) range[(int64_t)c * kRowBounds * P + threadIdx.x] = 0.f;
+    if (threadIdx.x != 0) return;
+    int far = 0;
+    for (int p = 0; p < P; ++p) {
+        for (int w = 0; w < 4; ++w) {
+            hi = w ? fmaxf(hi, red[p][w][0]) : red[p][w][0];
+            lo = w ? fminf(lo, red[p][w][1]) : red[p][w][1];
+        }
+        if (hi > 0.f && !(hi < kPairSpread * lo)) far = 1;
     }
+    uneven[c] = far;
+}
+
+// The largest product of an antenna's weight and a sample's larger component in
+// kRangeChunk spectra (blockIdx.x) of an uneven channel (blockIdx.y), times the
+// 2 row_top[c] components that a window row gathers at most.
+constexpr int kRangeChunk = 32;
+template <int P>
+__global__ void __launch_bounds__(256) range_kernel(const uint8_t* __restrict__ samples, int64_t T, int C, int A,
+                                                    const float* __restrict__ peak, const int32_t* __restrict__ row_top,
+                                                    const int32_t* __restrict__ uneven, float* __restrict__ range) {
+    const int c = blockIdx.y;
+    if (!uneven[c]) return;
+    __shared__ float red[4][2];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, AP = A * P;
+    const int64_t t0 = (int64_t)blockIdx.x * kRangeChunk;
+    const int n = (int)(t0 + kRangeChunk < T ? kRangeChunk : T - t0);
+    float m = 0.f;   // of the thread's pol: the block's size is even
+    for (int k = threadIdx.x; k < AP; k += 256) {
+        const uint8_t* src = samples + (t0 * C + c) * AP + k;
+        float most = 0.f;
+        for (int u = 0; u < n; ++u) {
+            const float2 v = unpack44(src[(int64_t)u * C * AP], 0);
+            most = fmaxf(most, fmaxf(fabsf(v.x), fabsf(v.y)));
+        }
+        if (most > 0.f) m = fmaxf(m, most * peak[(int64_t)c * AP + k]);
+    }
+    for (int x = 32; x >= P; x >>= 1) m = fmaxf(m, __shfl_xor(m, x));
+    if (lane < P) red[wv][lane] = m;
+    __syncthreads();
+    if (threadIdx.x >= P) return;
+    const int p = threadIdx.x;
+    m = fmaxf(fmaxf(red[0][p], red[1][p]), fmaxf(red[2][p], red[3][p]));
+    // as integers: they order like the values
+    atomicMax(reinterpret_cast<unsigned int*>(range) + (int64_t)c * kRowBounds * P + p,
+              __float_as_uint(2.0f * (float)row_top[c] * m));
+}
+
+// The smaller bound of each channel and pol: the samples' (0: none), or the
+// largest of the rows' by the weights alone.
+__global__ void range_end_kernel(const float* __restrict__ row_bound, int C, int P, float* __restrict__ range) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= C * P) return;
+    const int64_t c = k / P, p = k - c * P;
+    const float* in = row_bound + c * kRowBounds * P + p;
+    float* out = range + c * kRowBounds * P + p;
+    float m = 0.f;
+    for (int r = 0; r < kRowBounds; ++r) m = fmaxf(m, in[r * P]);
+    out[0] = out[0] > 0.f ? fminf(m, out[0]) : m;
+    for (int r = 1; r < kRowBounds; ++r) out[r * P] = 0.f;
 }
 
 // ---- autocorrelations (the a = b terms of Eq. 3) ---------------------------
@@ -566,11 +689,12 @@ hipError_t launch_twiddles(const SubDev& d, hipStream_t st) {
 hipError_t launch_weights(const SubDev& d, hipStream_t st) {
     const GatherProgram g0{d.chans, d.cells_desc, d.grp_ant, d.grp_tap, d.grp_w};
     const GatherProgram g1{d.pair_chans, d.pair_desc, d.pair_ant, d.pair_tap, d.pair_w};
-    const int n_slice = (d.CellMax + 63) / 64;
-    const int nb0 = d.grp_w ? (d.Gmax * kGroup + 255) / 256 : 0, nb1 = d.pair_w ? n_slice : 0;
-    const dim3 grid(nb0 + nb1, d.C), block(256);
+    const int nb0 = d.grp_w ? (d.Gmax * kGroup + 255) / 256 : 0, nb1 = d.pair_w ? (d.CellMax + 63) / 64 : 0;
+    const int nb2 = d.row_bound ? kRowBounds + (d.A * d.P + 31) / 32 : 0;
+    const dim3 grid(nb0 + nb1 + nb2, d.C), block(256);
 #define EPIC_WEIGHTS(PP, WM) \
-    weights_kernel<PP, WM><<<grid, block, 0, st>>>(g0, nb0, g1, d.taps, d.gains, d.A, d.K, d.gmag, n_slice)
+    weights_kernel<PP, WM><<<grid, block, 0, st>>>(g0, nb0, g1, nb1, d.taps, d.gains, d.cells, d.A, d.K, d.row_bound, \
+                                                   d.peak)
     if (d.P == 2) {
         if (d.wmode == kWComplex) EPIC_WEIGHTS(2, kWComplex);
         else if (d.wmode == kWReal) EPIC_WEIGHTS(2, kWReal);
@@ -580,6 +704,19 @@ hipError_t launch_weights(const SubDev& d, hipStream_t st) {
         else EPIC_WEIGHTS(1, kWReal);
     }
 #undef EPIC_WEIGHTS
+    return hipGetLastError();
+}
+
+hipError_t launch_range(const SubDev& d, const uint8_t* samples, int64_t n_time, hipStream_t st) {
+    const dim3 grid((unsigned)((n_time + kRangeChunk - 1) / kRangeChunk), d.C);
+    if (d.P == 2) {
+        range_start_kernel<2><<<dim3(d.C), dim3(256), 0, st>>>(d.peak, d.A, d.range, d.uneven);
+        range_kernel<2><<<grid, dim3(256), 0, st>>>(samples, n_time, d.C, d.A, d.peak, d.row_top, d.uneven, d.range);
+    } else {
+        range_start_kernel<1><<<dim3(d.C), dim3(256), 0, st>>>(d.peak, d.A, d.range, d.uneven);
+        range_kernel<1><<<grid, dim3(256), 0, st>>>(samples, n_time, d.C, d.A, d.peak, d.row_top, d.uneven, d.range);
+    }
+    range_end_kernel<<<dim3((d.C * d.P + 255) / 256), dim3(256), 0, st>>>(d.row_bound, d.C, d.P, d.range);
     return hipGetLastError();
 }
 

@@ -16,15 +16,24 @@
 // for two additions per output.
 //
 // FP32 on FP16 products (SPLIT).  Every operand x is held as hi = fp16(x) and
-// lo = fp16(x - hi), together accurate to about 2^-24.5 rms (an FP32 rounding
-// is 2^-24.8), and x y is summed in FP32 as hi hi' + lo hi' + hi lo'; the
-// dropped lo lo' is below 2^-23.5 rms of a product.  The depth of a product is
+// lo = fp16(x - hi), 22 to 23 bits of it (2^-24.5 rms; an FP32 rounding is
+// 2^-24.8), and x y is summed in FP32 as hi hi' + lo hi' + hi lo'; the dropped
+// lo lo' is below 2^-23.5 rms of a product.  The depth of a product is
 // the window's cells once per term, packed without padding between the terms:
 // the data operand stores [hi | lo] and is read cyclically ([hi | lo | hi]), the
 // DFT operand holds [hi | hi | lo].  Gridded values are scaled by a power of
-// two per channel and pol, and the DFT matrix by 16, to keep every part inside
-// FP16's normal range; the sums are scaled back when they leave the registers
-// (all exact).  In the FP16 form (no SPLIT) operands are rounded to FP16 once.
+// two per channel and pol, and the DFT matrix by 16; the sums are scaled back
+// when they leave the registers (all exact).  A scaled value below 2^-3 has a
+// subnormal lo: from there on its error is 2^-25 of the scaled unit and no
+// longer follows the value.  The scale is therefore the largest that a bound of
+// the window's rows allows (pair_scale), so that such values are small against
+// the rest: row sums of the weights, which a crowd of antennas in one cell does
+// not multiply by the window's width (2000 antennas in a cell, 60 outriggers in
+// 61 x 63 cells, samples of 0 and +-1: 0.6e-6 from 64-bit images, 5.8e-6 with the
+// largest cell's sum times the width), and, where the antennas' weights differ
+// by kPairSpread or more, the samples they meet in the call (range_kernel): a
+// silent antenna with a gain of 1e6 among 256 put the images off by 2e-4.  In the
+// FP16 form (no SPLIT) operands are rounded to FP16 once.
 //
 // A workgroup holds one spectrum at a time: gather -> row pass (the window's
 // rows times the DFT, i pairs) -> column pass (the DFT times the columns, j
@@ -138,8 +147,7 @@ struct PairArgs {
     const uint2* grp_ant;     // 4 x u16 per group
     const float4* grp_w;
     const _Float16* dft;      // [planes][TR][32 ST]
-    const float* gmag;        // [C][n_slice][P] largest sum of |weights| of a slice's cells (SPLIT)
-    int n_slice;
+    const float* row_bound;   // [C][kRowBounds][P] bounds of |Re G| + |Im G| summed over a window row (SPLIT)
     float* slots;             // [S][C][NPP][N][N]
     int64_t T;
     int C, A;
@@ -173,17 +181,15 @@ __device__ __forceinline__ void put_part4(_Float16* dst, const floatx4 v, float 
     }
 }
 
-// Scale of the gridded values of one pol, mag_bits the bits of the largest sum
-// of |w_re| + |w_im| over a cell's entries: the largest power of two for which
-// neither a gridded component (at most 8 times that sum) nor, after the row
-// pass, the sum of a window row of W cells times the scaled DFT operand (at most
-// W (|Re G| + |Im G|) 16) can leave half of FP16's range.
-__device__ __forceinline__ float pair_scale(int mag_bits, int W) {
-    const float bound = 16.0f * kDftScale * (float)W * __int_as_float(mag_bits);
-    if (!(bound > 0.0f)) return 1.0f;
-    int e = 15 - (((__float_as_int(bound) >> 23) & 255) - 126);   // bound < 2^(15 - e); inf: smallest scale
+// Scale of the gridded values of one pol: the largest power of two for which,
+// with row a bound of |Re G| + |Im G| summed over a window row, neither a
+// gridded component nor the row pass's sum of such a row times the scaled DFT
+// operand can leave half of FP16's range.
+__device__ __forceinline__ float pair_scale(int row_bits) {   // uniform: scalar registers
+    if (row_bits <= 0) return 1.0f;
+    int e = 15 - kDftScaleLog2 - (((row_bits >> 23) & 255) - 126);   // 16 row < 2^(15 - e); inf: smallest scale
     e = e > 100 ? 100 : (e < -100 ? -100 : e);
-    return __int_as_float(__builtin_amdgcn_readfirstlane((e + 127) << 23));   // uniform: a scalar register
+    return __int_as_float((e + 127) << 23);
 }
 
 // Decoded sample(s) of an antenna at an LDS address, FP16 (re, im per pol).
@@ -437,16 +443,17 @@ __attribute__((amdgpu_waves_per_eu(pair_waves<PairShape<N_, WD_, SPLIT, P>>())))
         const CellDesc* g_desc = a.desc + ci.cell_off;
         const uint2* g_ant = a.grp_ant + ci.grp_off;
         const float4* g_w = a.grp_w + (int64_t)ci.grp_off * GF4;
-        // the scales' magnitudes are loaded here and reduced after the copies below
-        float mx = 0.f, my = 0.f;
-        if constexpr (SPLIT)
-            for (int k = lane; k < (n_cell + 63) / 64; k += 64) {
-                const float* m = a.gmag + ((int64_t)c * a.n_slice + k) * P;
-                mx = fmaxf(mx, m[0]);
-                my = fmaxf(my, m[P - 1]);
-            }
+        // with products of three steps and more, registers are too few to keep
+        // what a lane number gives in this segment's loads over the whole kernel
+        // (N = 192, 44 x 44 cells, both pols: 720 us with, 509 without; station,
+        // two steps: 564 with, 575 without)
+        const int ls = ST > 2 ? opaque(lane) : lane;
+        // the rows' bounds, a lane each, are loaded here and reduced after the
+        // copies below
+        float most = 0.f;
+        if constexpr (SPLIT) most = a.row_bound[(int64_t)c * kRowBounds * P + (ls & (kRowBounds * P - 1))];
         CellDesc d0 = make_uint2(0u, 0u);   // of the wave's first slice
-        if (64 * wave < n_cell) d0 = g_desc[64 * wave + lane];
+        if (64 * wave < n_cell) d0 = g_desc[64 * wave + ls];
         __syncthreads();   // the previous segment is done with every LDS buffer
         const int ptid = opaque(tid);
         if constexpr (PROG) {
@@ -503,12 +510,9 @@ __attribute__((amdgpu_waves_per_eu(pair_waves<PairShape<N_, WD_, SPLIT, P>>())))
         float sx = 1.f, sy = 1.f;   // scale of the gridded values per pol
         if constexpr (SPLIT) {
 #pragma unroll
-            for (int x = 32; x > 0; x >>= 1) {
-                mx = fmaxf(mx, __shfl_xor(mx, x));
-                my = fmaxf(my, __shfl_xor(my, x));
-            }
-            sx = pair_scale(__builtin_amdgcn_readfirstlane(__float_as_int(mx)), ci.W);
-            sy = pair_scale(__builtin_amdgcn_readfirstlane(__float_as_int(my)), ci.W);
+            for (int x = P; x < kRowBounds * P; x *= 2) most = fmaxf(most, __shfl_xor(most, x));
+            sx = pair_scale(__builtin_amdgcn_readlane(__float_as_int(most), 0));
+            sy = pair_scale(__builtin_amdgcn_readlane(__float_as_int(most), P - 1));
         }
         asm volatile("" : "+v"(d0.x), "+v"(d0.y));   // arrived before the loop
         __syncthreads();
@@ -967,8 +971,7 @@ hipError_t launch_pair(const SubDev& d, const uint8_t* samples, int64_t n_time, 
     a.grp_ant = reinterpret_cast<const uint2*>(d.pair_ant);
     a.grp_w = reinterpret_cast<const float4*>(d.pair_w);
     a.dft = reinterpret_cast<const _Float16*>(d.pair_dft);
-    a.gmag = d.gmag;
-    a.n_slice = (d.CellMax + 63) / 64;
+    a.row_bound = d.use_range ? d.range : d.row_bound;
     a.slots = d.slots;
     a.T = n_time;
     a.C = d.C; a.A = d.A;

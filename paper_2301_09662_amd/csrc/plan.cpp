@@ -12,6 +12,7 @@
 #include <limits>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <set>
 #include <string>
 #include <vector>
@@ -89,6 +90,11 @@ struct SubHost {
     std::vector<SubDev> cands;
     SubDev dev{};
     SubDev ef{};                     // FP32: launch shape of the E-field kernel
+    // FP32 scales: most entries of a window row per channel, largest user tap per
+    // (channel, antenna, pol), and whether the weights in effect are uneven
+    std::vector<int32_t> row_top;
+    std::vector<float> tap_peak;
+    bool uneven = false;
 };
 
 }  // namespace
@@ -124,6 +130,7 @@ struct epic_plan_s {
     struct GraphEntry {
         int64_t T;
         int fresh;
+        uint32_t ranged;
         std::vector<const uint8_t*> ptrs;
         hipGraph_t graph;
         hipGraphExec_t exec;
@@ -137,6 +144,7 @@ struct epic_plan_s {
     std::vector<int64_t> ac_pending;
     int64_t ac_limit = 0;
     int ac_captured = 0;   // an accumulate call was captured by the caller: replays go uncounted
+    int gains_captured = 0;   // a set_gains call was: replays change the weights unseen
     // host staging of epic_set_gains (pinned, reused once its copy is done)
     float* gain_stage = nullptr;
     size_t gain_stage_n = 0;
@@ -201,6 +209,7 @@ void build_gather(SubHost& h) {
     const epic_array_desc& s = h.desc;
     const int A = s.n_ant, C = s.n_chan, K = s.kernel_k, hk = K / 2;
     h.chans.assign(C, ChanInfo{});
+    h.row_top.assign(C, 0);
     int Rmax = 0, Wmax = 0;
     for (int c = 0; c < C; ++c) {
         const int32_t* cc = &h.cells[(size_t)c * A * 2];
@@ -267,6 +276,8 @@ void build_gather(SubHost& h) {
                     h.grp_tap[e] = (uint8_t)(dy * K + dx);
                 }
             }
+        for (int r = 0; r < ci.R; ++r)
+            h.row_top[c] = std::max(h.row_top[c], std::accumulate(&count[(size_t)r * ci.W], &count[(size_t)r * ci.W] + ci.W, 0));
         ci.n_grp = (int32_t)g;
         Gmax = std::max(Gmax, ci.n_grp);
         CellMax = std::max(CellMax, ci.n_cell);
@@ -770,12 +781,70 @@ epic_status autotune_batch(epic_plan_s* p, hipStream_t st, bool choose_form) {
 hipError_t launch_one(const SubDev& d, const uint8_t* samples, int64_t n_time, hipStream_t st) {
     if (d.gridder == EPIC_GRID_DIRECT_GEMM) return launch_direct(d, samples, n_time, st);
     if (d.gridder != EPIC_GRID_GATHER) return launch_bgemm(d, samples, n_time, st);
-    if (d.pair) return launch_pair(d, samples, n_time, st);
+    if (d.pair) {
+        hipError_t e = d.use_range ? launch_range(d, samples, n_time, st) : hipSuccess;
+        return e == hipSuccess ? launch_pair(d, samples, n_time, st) : e;
+    }
     return launch_fp32(d, samples, n_time, st);
 }
 
+// Largest |re| + |im| of the user's taps per (channel, antenna, pol).
+void set_tap_peaks(SubHost& h) {
+    const size_t kk = (size_t)h.desc.kernel_k * h.desc.kernel_k * 2;
+    h.tap_peak.assign(h.user_taps.size() / kk, 0.f);
+    for (size_t q = 0; q < h.tap_peak.size(); ++q)
+        for (size_t k = 0; k < kk; k += 2)
+            h.tap_peak[q] = std::max(h.tap_peak[q], std::fabs(h.user_taps[q * kk + k]) + std::fabs(h.user_taps[q * kk + k + 1]));
+}
+
+// Whether the antennas of some channel and pol weigh so differently that the
+// FP32 scales have to go by the samples: gains (null: 1) times tap peaks, zeros
+// left out.  The default Gaussians' own peaks are within a factor of four of
+// each other and are not counted.
+bool weights_uneven(const SubHost& h, const float* gains) {
+    const int64_t A = h.desc.n_ant, P = h.desc.n_pol, C = h.desc.n_chan;
+    if (!gains && h.tap_peak.empty()) return false;
+    for (int64_t c = 0; c < C; ++c)
+        for (int64_t p = 0; p < P; ++p) {
+            float hi = 0.f, lo = std::numeric_limits<float>::infinity();
+            for (int64_t a = 0; a < A; ++a) {
+                const int64_t q = (c * A + a) * P + p;
+                float w = gains ? std::max(std::fabs(gains[2 * q]), std::fabs(gains[2 * q + 1])) : 1.f;
+                if (!h.tap_peak.empty()) w *= h.tap_peak[q];
+                hi = std::max(hi, w);
+                if (w > 0.f) lo = std::min(lo, w);
+            }
+            if (hi > 0.f && !(hi < 0.5f * kPairSpread * lo)) return true;
+        }
+    return false;
+}
+
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
+
+// The sub-arrays (bits) whose FP32 scales go by the samples in this call: those
+// with uneven weights.  What the caller captures is replayed under gains not
+// known here, so it holds the look at the samples in any case; its kernels
+// leave the channels with even weights alone.
+uint32_t ranged_subs(const epic_plan_s* p, hipStream_t st) {
+    uint32_t bits = 0, pairs = 0;
+    for (size_t k = 0; k < p->subs.size(); ++k) {
+        const SubHost& h = p->subs[k];
+        if (!h.dev.range) continue;
+        pairs |= 1u << k;
+        if (h.uneven || p->gains_captured) bits |= 1u << k;
+    }
+    return bits != pairs && capturing(st) ? pairs : bits;
+}
+
 // The kernel launches of one accumulate step.
-hipError_t launch_step(epic_plan_s* p, const uint8_t* const* d_samples, int64_t n_time, hipStream_t st) {
+hipError_t launch_step(epic_plan_s* p, const uint8_t* const* d_samples, int64_t n_time, uint32_t ranged, hipStream_t st) {
     if (p->batched) {
         BatchDev bd = p->bd;
         bd.fresh = p->slots_zero;
@@ -785,6 +854,7 @@ hipError_t launch_step(epic_plan_s* p, const uint8_t* const* d_samples, int64_t 
         for (size_t k = 0; k < p->subs.size(); ++k) {
             SubDev d = p->subs[k].dev;
             d.fresh = p->slots_zero;
+            d.use_range = (ranged >> k) & 1;
             hipError_t e = launch_one(d, d_samples[k], n_time, st);
             if (e != hipSuccess) return e;
         }
@@ -816,11 +886,12 @@ bool one_kernel_step(const epic_plan_s* p) {
     return true;
 }
 
-hipError_t launch_step_graph(epic_plan_s* p, const uint8_t* const* d_samples, int64_t n_time, hipStream_t st) {
+hipError_t launch_step_graph(epic_plan_s* p, const uint8_t* const* d_samples, int64_t n_time, uint32_t ranged,
+                             hipStream_t st) {
     std::vector<const uint8_t*> ptrs(d_samples, d_samples + p->subs.size());
     epic_plan_s::GraphEntry* hit = nullptr;
     for (auto& g : p->graphs)
-        if (g.T == n_time && g.fresh == p->slots_zero && g.ptrs == ptrs) hit = &g;
+        if (g.T == n_time && g.fresh == p->slots_zero && g.ranged == ranged && g.ptrs == ptrs) hit = &g;
     if (!hit) {
         if (p->graphs.size() >= kGraphCache) {
             auto lru = std::min_element(p->graphs.begin(), p->graphs.end(),
@@ -829,11 +900,11 @@ hipError_t launch_step_graph(epic_plan_s* p, const uint8_t* const* d_samples, in
             if (lru->graph) (void)hipGraphDestroy(lru->graph);
             p->graphs.erase(lru);
         }
-        epic_plan_s::GraphEntry g{n_time, p->slots_zero, ptrs, nullptr, nullptr, 0};
+        epic_plan_s::GraphEntry g{n_time, p->slots_zero, ranged, ptrs, nullptr, nullptr, 0};
         if (!one_kernel_step(p)) {
             hipError_t e = hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return e;
-            hipError_t le = launch_step(p, d_samples, n_time, p->cap_stream);
+            hipError_t le = launch_step(p, d_samples, n_time, ranged, p->cap_stream);
             e = hipStreamEndCapture(p->cap_stream, &g.graph);
             if (le != hipSuccess || e != hipSuccess) {
                 if (g.graph) (void)hipGraphDestroy(g.graph);
@@ -850,7 +921,7 @@ hipError_t launch_step_graph(epic_plan_s* p, const uint8_t* const* d_samples, in
         hit = &p->graphs.back();
     }
     hit->last = ++p->graph_clock;
-    return hit->exec ? hipGraphLaunch(hit->exec, st) : launch_step(p, d_samples, n_time, st);
+    return hit->exec ? hipGraphLaunch(hit->exec, st) : launch_step(p, d_samples, n_time, ranged, st);
 }
 
 // Zero-lag sums about to pass the exact int32 range: fold them into the lag
@@ -1262,7 +1333,15 @@ epic_status make_plan(const epic_plan_desc* desc, hipStream_t st, epic_plan_s* p
             ar.add(&d.pair_tap, h.pair_tap);
             ar.add(&d.pair_w, h.pair_ant.size() * 2 * (size_t)d.P);
             ar.add(&pair_dft, (size_t)pair_table_halfs(d));
-            if (d.precision == EPIC_FP32) ar.add(&d.gmag, (size_t)d.C * ((d.CellMax + 63) / 64) * d.P);
+            if (d.precision == EPIC_FP32) {
+                ar.add(&d.row_top, h.row_top);
+                ar.add(&d.row_bound, (size_t)d.C * kRowBounds * d.P);
+                ar.add(&d.peak, (size_t)d.C * d.A * d.P);
+                ar.add(&d.range, (size_t)2 * d.C * kRowBounds * d.P);
+                ar.add(&d.uneven, (size_t)2 * d.C);
+                set_tap_peaks(h);
+                h.uneven = weights_uneven(h, nullptr);
+            }
         }
         if (need_dir) ar.add(&dir_m, (size_t)direct_matrix_halfs(d));
         d.bg_nterm = d.precision == EPIC_FP8 ? 3 : 2;
@@ -1440,15 +1519,12 @@ epic_status epic_grid_fft_accumulate(epic_plan_t p, const uint8_t* const* d_samp
         if (!d_samples[k]) return EPIC_E_ARG;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (hipSetDevice(p->device) != hipSuccess) return check_device(p, hipErrorInvalidDevice);
-    if ((p->desc.flags & EPIC_F_REMOVE_AUTOCORR) && !p->ac_captured) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
-        else if (cs != hipStreamCaptureStatusNone) p->ac_captured = 1;
-    }
+    if ((p->desc.flags & EPIC_F_REMOVE_AUTOCORR) && !p->ac_captured && capturing(st)) p->ac_captured = 1;
+    const uint32_t ranged = ranged_subs(p, st);
     hipError_t e = autocorr_guard(p, n_time, st);
     if (e == hipSuccess)
-        e = (p->desc.flags & EPIC_F_GRAPH) ? launch_step_graph(p, d_samples, n_time, st)
-                                           : launch_step(p, d_samples, n_time, st);
+        e = (p->desc.flags & EPIC_F_GRAPH) ? launch_step_graph(p, d_samples, n_time, ranged, st)
+                                           : launch_step(p, d_samples, n_time, ranged, st);
     if (e == hipSuccess) p->slots_zero = 0;
     return check_device(p, e);
 }
@@ -1539,9 +1615,15 @@ epic_status epic_image_noalloc(epic_plan_t p, const uint8_t* const* d_samples, i
     float* base = nullptr;
     hipError_t e = scratch_address(p->device, &base);
     if (e != hipSuccess) return check_device(p, e);
+    const uint32_t ranged = ranged_subs(p, st);
     for (size_t k = 0; k < run.size(); ++k) {
         run[k].slots = base + off[k];
         run[k].fresh = 1;   // every slot that the read-out sums is stored by this call
+        run[k].use_range = (ranged >> k) & 1;
+        if (run[k].use_range) {   // this call's own: an accumulate call may run on another stream
+            run[k].range += (size_t)run[k].C * kRowBounds * run[k].P;
+            run[k].uneven += run[k].C;
+        }
     }
     for (size_t k = 0; k < run.size() && e == hipSuccess && n_time > 0; ++k) {
         const SubDev& d = run[k];
@@ -1578,6 +1660,10 @@ epic_status epic_set_gains(epic_plan_t p, int32_t sub, const float* h_gains, voi
     if (p->ac_pending[sub] > 0 || p->ac_captured) e = launch_autocorr_fold(d, st);
     if (e != hipSuccess) return check_device(p, e);
     p->ac_pending[sub] = 0;
+    if (d.range) {
+        if (!p->gains_captured && capturing(st)) p->gains_captured = 1;
+        p->subs[sub].uneven = weights_uneven(p->subs[sub], h_gains);
+    }
     if (!h_gains) {
         d.gains = nullptr;
     } else {

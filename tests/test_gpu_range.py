@@ -1,0 +1,205 @@
+"""FP32 images of arrays whose antennas or cells weigh very differently: heavy
+antennas that are silent, live only later, or crowded into one cell.
+
+The bar is 1e-6, a tenth of the library's FP32 bar.  FP32 sums of the gridded
+cells and of the transform leave a few 2^-24 of the field's rms; the split FP16
+operands add at most 2.7e-10 of the largest sum of |weights| over a window row
+per cell, which for the arrays here is below 2^-24 of that rms too, provided the
+scales do not follow weights that meet no samples.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+from coverage_layouts import C0, box
+from gpu_util import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-6
+
+
+@pytest.fixture(scope="module")
+def E():
+    from paper_2301_09662_amd import epic
+    return epic
+
+
+def station(n_chan=2, n_pol=2, n_ant=256):
+    s = dataclasses.replace(box(64, 18, 17, P=n_pol, n_extra=n_ant - 2, seed=7), n_chan=n_chan)
+    return s
+
+
+def rand(s, T, seed):
+    return np.random.default_rng(seed).integers(0, 256, (T, s.n_chan, s.n_ant, s.n_pol), dtype=np.uint8)
+
+
+def ref_image(s, x, g):
+    """The oracle's images under gains g, and the taps times g."""
+    t = oracle.taps(s) * (g[..., 0] + 1j * g[..., 1].astype(np.float64))[..., None, None]
+    return oracle.image(s, x, taps=np.stack([t.real, t.imag], axis=-1).astype(np.float32)), t
+
+
+def run(E, s, x, gains=None, flags=0, calls=None, noalloc=False, taps=None):
+    import torch
+    T = x.shape[0]
+    d = torch.from_numpy(x).cuda()
+    out = torch.empty((s.n_chan, 4 if s.n_pol == 2 else 1, s.grid_n, s.grid_n), device="cuda")
+    plan = E.epic_plan([s], max_time=T, flags=flags, taps=None if taps is None else [taps])
+    try:
+        if gains is not None:
+            E.epic_set_gains(plan, 0, gains)
+        if noalloc:
+            E.epic_image_noalloc(plan, [d], T, [out])
+        else:
+            t = 0
+            for n in calls or [T]:
+                E.epic_grid_fft_accumulate(plan, [d[t:t + n]], n)
+                t += n
+            E.epic_readout(plan, [out], 1)
+        return out.double().cpu().numpy()
+    finally:
+        E.epic_destroy(plan)
+
+
+@pytest.mark.parametrize("heavy", [1e3, 1e4, 1e6, 1e8])
+@pytest.mark.parametrize("mode", ["real", "complex", "noalloc", "taps", "single", "calls"])
+def test_silent_antenna_of_any_gain(E, mode, heavy):
+    """One antenna without samples whose gain blew up, in one channel of two."""
+    s = station(n_pol=1 if mode == "single" else 2)
+    x = rand(s, 6, 3)
+    x[:, :, 100] = 0
+    g = np.zeros((s.n_chan, s.n_ant, s.n_pol, 2), np.float32)
+    g[..., 0] = 1
+    if mode == "complex":
+        ph = np.random.default_rng(4).uniform(-np.pi, np.pi, g.shape[:3])
+        g[..., 0], g[..., 1] = np.cos(ph), np.sin(ph)
+    g[1, 100] *= np.float32(heavy)
+    ref, t = ref_image(s, x, g)
+    if mode == "taps":
+        got = run(E, s, x, taps=np.stack([t.real, t.imag], axis=-1).astype(np.float32))
+    else:
+        got = run(E, s, x, g, flags=E.EPIC_F_COMPLEX_WEIGHTS if mode == "complex" else 0, noalloc=mode == "noalloc",
+                  calls=[1, 3, 2] if mode == "calls" else None)
+    assert_parity(got, ref, TOL, f"{mode} {heavy:g}")
+
+
+@pytest.mark.parametrize("first", [0, 1, 5])
+def test_heavy_antenna_from_some_spectrum_on(E, first):
+    """Silent at first, then live: no gridded value leaves the range.  The
+    spectra before are 1e-10 of the image, those after carry it."""
+    s = station()
+    x = rand(s, 40, 5)
+    x[:first, :, 100] = 0
+    g = np.zeros((s.n_chan, s.n_ant, 2, 2), np.float32)
+    g[..., 0] = 1
+    g[:, 100, :, 0] = 1e5
+    assert_parity(run(E, s, x, g), ref_image(s, x, g)[0], TOL, f"live from {first}")
+
+
+def test_one_pol_silent(E):
+    """No samples in Y, and none at all in a channel."""
+    s = station()
+    x = rand(s, 20, 6)
+    x[..., 1] = 0
+    x[:, 1] = 0
+    g = np.zeros((s.n_chan, s.n_ant, 2, 2), np.float32)
+    g[..., 0] = np.random.default_rng(1).uniform(0.01, 100, g.shape[:3])
+    got = run(E, s, x, g, flags=E.EPIC_F_COMPLEX_WEIGHTS)
+    ref = ref_image(s, x, g)[0]
+    assert (got[1] == 0).all() and (got[0, 1:] == 0).all()
+    assert np.abs(got[0, 0] - ref[0, 0]).max() <= TOL * ref[0, 0].max()
+
+
+@pytest.mark.parametrize("heavy", [1e4, 1e8])
+def test_silent_antenna_with_autocorrelations_removed(E, heavy):
+    s = station()
+    x = rand(s, 6, 8)
+    x[:, :, 100] = 0
+    g = np.zeros((s.n_chan, s.n_ant, 2, 2), np.float32)
+    g[..., 0] = 1
+    g[1, 100] *= np.float32(heavy)
+    got = run(E, s, x, g, flags=E.EPIC_F_REMOVE_AUTOCORR)
+    full, t = ref_image(s, x, g)
+    taps = np.stack([t.real, t.imag], axis=-1).astype(np.float32)
+    ref = full - oracle.autocorr(s, x, taps=taps)
+    for c in range(s.n_chan):
+        assert np.abs(got[c] - ref[c]).max() <= TOL * np.abs(full[c]).max(), c
+
+
+@pytest.mark.parametrize("low", [0, 1])
+@pytest.mark.parametrize("N,crowd", [(64, 250), (64, 2000), (128, 250), (128, 2000)])
+def test_crowded_cell_and_outriggers(E, N, crowd, low):
+    """A crowd of antennas in one cell, sixty others all over a 61 x 63 window,
+    samples of every value or of components -1, 0 and 1 only."""
+    wide = box(N, 61, 63, P=1, n_extra=58, seed=11)
+    rng = np.random.default_rng(12)
+    near = np.array([[2.0, -3.0]]) + rng.uniform(-0.4, 0.4, (crowd, 2))
+    s = dataclasses.replace(wide, ant_xy=np.concatenate([wide.ant_xy, near * (C0 / 40e6)]))
+    x = rand(s, 5, 13)
+    if low:
+        x = np.array([0x00, 0x01, 0x0F, 0x10, 0xF0, 0x11, 0xFF, 0x1F], np.uint8)[x & 7]
+    got, ref = run(E, s, x), oracle.image(s, x)
+    assert_parity(got, ref, TOL, f"crowd of {crowd}")
+
+
+def test_captured_calls_follow_later_gains(E):
+    """A caller's graph of one integration, captured under even gains and
+    replayed under others: a silent antenna of gain 1e6, and back."""
+    import torch
+    s = station()
+    x = rand(s, 6, 14)
+    x[:, :, 100] = 0
+    d = torch.from_numpy(x).cuda()
+    out = torch.empty((s.n_chan, 4, 64, 64), device="cuda")
+    even = np.zeros((s.n_chan, s.n_ant, 2, 2), np.float32)
+    even[..., 0] = 1
+    odd = even.copy()
+    odd[1, 100] *= np.float32(1e6)
+    plan = E.epic_plan([s], max_time=6)
+    try:
+        E.epic_set_gains(plan, 0, even)
+        E.epic_grid_fft_accumulate(plan, [d], 6)
+        E.epic_readout(plan, [out], 1)
+        torch.cuda.synchronize()
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=side):
+            E.epic_image_noalloc(plan, [d], 6, [out], side)
+        for g in (even, odd, even, odd):
+            E.epic_set_gains(plan, 0, g)
+            torch.cuda.synchronize()
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert_parity(out.double().cpu().numpy(), ref_image(s, x, g)[0], TOL, "replay")
+    finally:
+        E.epic_destroy(plan)
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+def test_gains_changed_between_calls(E, graph):
+    """Two sub-arrays, one with uneven gains for a while, with and without the
+    library's own graphs."""
+    import torch
+    subs = [station(), station(n_chan=1, n_pol=1, n_ant=40)]
+    xs = [rand(s, 6, 15 + k) for k, s in enumerate(subs)]
+    xs[0][:, :, 100] = 0
+    ds = [torch.from_numpy(x).cuda() for x in xs]
+    outs = [torch.empty((s.n_chan, 4 if s.n_pol == 2 else 1, 64, 64), device="cuda") for s in subs]
+    even = np.zeros((2, 256, 2, 2), np.float32)
+    even[..., 0] = 1
+    odd = even.copy()
+    odd[1, 100] *= np.float32(1e6)
+    plan = E.epic_plan(subs, max_time=6, flags=E.EPIC_F_GRAPH if graph else 0)
+    try:
+        for g in (even, odd, even, odd):
+            E.epic_set_gains(plan, 0, g)
+            E.epic_grid_fft_accumulate(plan, ds, 6)
+            E.epic_readout(plan, outs, 1)
+            torch.cuda.synchronize()
+            assert_parity(outs[0].double().cpu().numpy(), ref_image(subs[0], xs[0], g)[0], TOL, "uneven")
+            assert_parity(outs[1].double().cpu().numpy(), oracle.image(subs[1], xs[1]), TOL, "even")
+    finally:
+        E.epic_destroy(plan)

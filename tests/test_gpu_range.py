@@ -99,6 +99,36 @@ def test_heavy_antenna_from_some_spectrum_on(E, first):
     assert_parity(run(E, s, x, g), ref_image(s, x, g)[0], TOL, f"live from {first}")
 
 
+@pytest.mark.parametrize("n_ant,n_pol,offset", [(37, 2, 0), (37, 1, 0), (300, 2, 2), (1100, 1, 1), (1100, 1, 0), (513, 2, 0)])
+@pytest.mark.parametrize("n_time", [1, 67])
+def test_rows_of_any_length_and_address(E, n_ant, n_pol, offset, n_time):
+    """The look at the samples by words and by bytes; the heavy antenna speaks
+    once, in the last spectrum, or never."""
+    import torch
+    s = station(n_pol=n_pol, n_ant=n_ant)
+    for spoken in (0, 1):
+        x = rand(s, n_time, 20)
+        x[:, :, n_ant - 1] = 0
+        if spoken:
+            x[-1, :, n_ant - 1] = 0x80   # -8
+        g = np.zeros((2, n_ant, n_pol, 2), np.float32)
+        g[..., 0] = 1
+        g[:, n_ant - 1, :, 0] = 1e6
+        buf = torch.zeros(x.size + 8, dtype=torch.uint8, device="cuda")
+        d = buf[offset:offset + x.size].view(x.shape)
+        d.copy_(torch.from_numpy(x))
+        out = torch.empty((2, 4 if n_pol == 2 else 1, 64, 64), device="cuda")
+        plan = E.epic_plan([s], max_time=n_time)
+        try:
+            E.epic_set_gains(plan, 0, g)
+            E.epic_grid_fft_accumulate(plan, [d], n_time)
+            E.epic_readout(plan, [out], 1)
+            got = out.double().cpu().numpy()
+        finally:
+            E.epic_destroy(plan)
+        assert_parity(got, ref_image(s, x, g)[0], TOL, f"spoken {spoken}")
+
+
 def test_one_pol_silent(E):
     """No samples in Y, and none at all in a channel."""
     s = station()

@@ -143,7 +143,9 @@ struct epic_plan_s {
     // their last fold, and the count at which they are folded first
     std::vector<int64_t> ac_pending;
     int64_t ac_limit = 0;
-    int ac_captured = 0;   // an accumulate call was captured by the caller: replays go uncounted
+    // the caller captured an accumulate, read-out or set_gains call: what replays
+    // gather and what a captured call folds go uncounted
+    int ac_captured = 0;
     int gains_captured = 0;   // a set_gains call was: replays change the weights unseen
     // host staging of epic_set_gains (pinned, reused once its copy is done)
     float* gain_stage = nullptr;
@@ -826,6 +828,14 @@ bool capturing(hipStream_t st) {
         return false;
     }
     return cs != hipStreamCaptureStatusNone;
+}
+
+// Whether this call is being captured, on a plan with autocorrelation removal:
+// from then on the host's counts of the zero-lag sums are not relied on.
+bool captures_autocorr(epic_plan_s* p, hipStream_t st) {
+    if (!(p->desc.flags & EPIC_F_REMOVE_AUTOCORR) || !capturing(st)) return false;
+    p->ac_captured = 1;
+    return true;
 }
 
 // The sub-arrays (bits) whose FP32 scales go by the samples in this call: those
@@ -1519,7 +1529,7 @@ epic_status epic_grid_fft_accumulate(epic_plan_t p, const uint8_t* const* d_samp
         if (!d_samples[k]) return EPIC_E_ARG;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (hipSetDevice(p->device) != hipSuccess) return check_device(p, hipErrorInvalidDevice);
-    if ((p->desc.flags & EPIC_F_REMOVE_AUTOCORR) && !p->ac_captured && capturing(st)) p->ac_captured = 1;
+    (void)captures_autocorr(p, st);
     const uint32_t ranged = ranged_subs(p, st);
     hipError_t e = autocorr_guard(p, n_time, st);
     if (e == hipSuccess)
@@ -1559,10 +1569,11 @@ epic_status epic_readout(epic_plan_t p, float* const* d_images, int32_t reset, v
         if (!d_images[k]) return EPIC_E_ARG;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (hipSetDevice(p->device) != hipSuccess) return check_device(p, hipErrorInvalidDevice);
+    const bool recorded = captures_autocorr(p, st);
     for (size_t k = 0; k < p->subs.size(); ++k) {
         hipError_t e = launch_readout(p->subs[k].dev, d_images[k], p->desc.output == EPIC_OUT_STOKES, reset != 0, st);
         if (e != hipSuccess) return check_device(p, e);
-        if (!p->ac_pending.empty()) p->ac_pending[k] = 0;   // the read-out folded them
+        if (!recorded) p->ac_pending[k] = 0;   // the read-out folded them
     }
     if (reset) p->slots_zero = 1;
     return EPIC_OK;
@@ -1654,12 +1665,13 @@ epic_status epic_set_gains(epic_plan_t p, int32_t sub, const float* h_gains, voi
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (hipSetDevice(p->device) != hipSuccess) return check_device(p, hipErrorInvalidDevice);
     // the autocorrelations gathered so far belong to the old gains (none since
-    // the last fold: nothing to do, unless replays of a graph that the caller
-    // captured may have gathered some)
+    // the last fold: nothing to do, unless the caller captures or captured calls,
+    // which are not counted when they run)
+    const bool recorded = captures_autocorr(p, st);
     hipError_t e = hipSuccess;
     if (p->ac_pending[sub] > 0 || p->ac_captured) e = launch_autocorr_fold(d, st);
     if (e != hipSuccess) return check_device(p, e);
-    p->ac_pending[sub] = 0;
+    if (!recorded) p->ac_pending[sub] = 0;
     if (d.range) {
         if (!p->gains_captured && capturing(st)) p->gains_captured = 1;
         p->subs[sub].uneven = weights_uneven(p->subs[sub], h_gains);

@@ -289,8 +289,10 @@ epic_status epic_set_gains(epic_plan_t plan, int32_t sub, const float* h_gains, 
  * streams, other plans, other host threads) race and give wrong images.
  * Errors: EPIC_E_ARG, EPIC_E_STATE, EPIC_E_DEVICE; EPIC_E_NOMEM when the
  * plan's partial accumulators for n_time spectra, sum over sub-arrays of
- * S x C x NPP x N x N floats, exceed EPIC_NOALLOC_MAX_BYTES; EPIC_E_UNSUPPORTED
- * for plans with EPIC_F_REMOVE_AUTOCORR (whose zero-lag sums are plan state).
+ * S x C x NPP x N x N floats, exceed EPIC_NOALLOC_MAX_BYTES with S = 2 (1 for a
+ * single spectrum; the direct form's S is its time chunks);
+ * EPIC_E_UNSUPPORTED for plans with EPIC_F_REMOVE_AUTOCORR (whose zero-lag sums
+ * are plan state).
  */
 #define EPIC_NOALLOC_MAX_BYTES (64ll << 20)
 epic_status epic_image_noalloc(epic_plan_t plan, const uint8_t* const* d_samples, int64_t n_time,

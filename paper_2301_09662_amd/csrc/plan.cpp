@@ -1579,17 +1579,15 @@ epic_status epic_readout(epic_plan_t p, float* const* d_images, int32_t reset, v
     return EPIC_OK;
 }
 
-// Workgroups of a gather launch whose slots have to fit the static scratch: at
-// N = 32 (and FP32 at N = 48) the paired-transform kernel keeps up to twice the
-// workgroups on a CU that the row-by-row FP32 kernel does, and so up to one slot
-// more per channel (1400 channels, dual pol: 3 slots and 69 MB against 2 and
-// 46 MB).  A whole image in fewer workgroups beats none: FP32 takes the shape of
-// that kernel, FP16 three workgroups per CU.
-int narrow_grid(const epic_plan_s* p, const SubHost& h) {
-    const SubDev& d = h.dev;
-    if (d.gridder != EPIC_GRID_GATHER && d.precision != EPIC_FP32) return d.grid_wg;
-    const int wg = d.precision == EPIC_FP32 ? h.ef.grid_wg : 3 * p->num_cu;
-    return wg >= d.KS ? std::min(d.grid_wg, wg / d.KS * d.KS) : d.grid_wg;
+// Slots of d's launch of n_time spectra when it may have at most `most` (two or
+// more: pieces of a channel on one side and on the other of the border between
+// two workgroups), in as many workgroups as that allows.  The direct form's
+// slots are its time chunks and stay.
+void limit_slots(SubDev& d, int64_t n_time, int most) {
+    d.S = slots_for(d, n_time);
+    if (d.S <= most || (d.precision != EPIC_FP32 && d.gridder == EPIC_GRID_DIRECT_GEMM)) return;
+    d.grid_wg = (int)std::min<int64_t>(d.grid_wg, (int64_t)(most - 1) * d.C * d.KS);
+    d.S = slots_for(d, n_time);
 }
 
 epic_status epic_image_noalloc(epic_plan_t p, const uint8_t* const* d_samples, int64_t n_time,
@@ -1602,17 +1600,22 @@ epic_status epic_image_noalloc(epic_plan_t p, const uint8_t* const* d_samples, i
         if (!d_images[k] || (n_time > 0 && !d_samples[k])) return EPIC_E_ARG;
     if (p->desc.flags & EPIC_F_REMOVE_AUTOCORR) return EPIC_E_UNSUPPORTED;
     // partial accumulators of this call: each sub-array's slots for n_time
-    // spectra in its dedicated launch, packed into the static scratch; where
-    // they do not fit, in a launch of fewer workgroups
+    // spectra in its dedicated launch, packed into the static scratch.  Where
+    // they do not fit, in launches of fewer workgroups, down to two slots per
+    // channel: a whole image in fewer workgroups beats none, and how many share a
+    // CU (so how many slots a full launch has) is no reason to refuse a call
+    // (1400 channels, dual pol, N = 32: three slots and 69 MB, or two and 46 MB).
+    const int64_t T = std::max<int64_t>(n_time, 1);
     std::vector<SubDev> run(p->subs.size());
     std::vector<size_t> off(p->subs.size());
+    int most = 2;
+    for (const SubHost& h : p->subs) most = std::max(most, slots_for(h.dev, T));
     size_t need = 0;
-    for (int narrow = 0; narrow < 2; ++narrow) {
+    for (; most >= 2; --most) {
         need = 0;
         for (size_t k = 0; k < p->subs.size(); ++k) {
             SubDev d = p->subs[k].dev;
-            if (narrow) d.grid_wg = narrow_grid(p, p->subs[k]);
-            d.S = slots_for(d, std::max<int64_t>(n_time, 1));
+            limit_slots(d, T, most);
             d.vaa = nullptr;
             off[k] = need;
             need += ((size_t)d.S * d.C * d.NPP * d.N * d.N + 63) & ~(size_t)63;   // 256-byte aligned pieces

@@ -401,6 +401,15 @@ __global__ void __launch_bounds__(256) autocorr_words_kernel(const uint32_t* __r
     }
 }
 
+__device__ __forceinline__ float2 times(float2 v, float s) { return make_float2(v.x * s, v.y * s); }
+// Divides g by the power of two of its larger component and returns that.
+__device__ __forceinline__ float take_power(float2& g) {
+    int e = (__float_as_int(fmaxf(fabsf(g.x), fabsf(g.y))) >> 23) - 127;   // zero and subnormal: -127
+    e = e < -126 ? 0 : (e > 126 ? 126 : e);
+    g = times(g, __int_as_float((127 - e) << 23));
+    return __int_as_float((127 + e) << 23);
+}
+
 // Lag sums of one channel: R^{pq}(d) = sum_a V^{pq}_aa sum_u w^p_a(u + d) conj(w^q_a(u))
 // for every tap offset d in [-(K-1), K-1]^2 (the correlation of the antenna's
 // kernel with itself, weighted by its zero-lag correlation).  An antenna's
@@ -436,10 +445,17 @@ __global__ void __launch_bounds__(256) autocorr_lag_kernel(const int32_t* __rest
         const int64_t ca = (int64_t)c * A + a;
         const int32_t* v = vaa + ca * npa;
         const float2* t = reinterpret_cast<const float2*>(taps) + ca * P * K * K;
+        // a gain's power of two goes to the taps, exactly: their products stay in
+        // range wherever the weights' do
         float2 gx = make_float2(1.f, 0.f), gy = gx;
+        float tx = 1.f, ty = 1.f;
         if (gains) {
             gx = reinterpret_cast<const float2*>(gains)[ca * P];
-            if (P == 2) gy = reinterpret_cast<const float2*>(gains)[ca * P + 1];
+            tx = take_power(gx);
+            if (P == 2) {
+                gy = reinterpret_cast<const float2*>(gains)[ca * P + 1];
+                ty = take_power(gy);
+            }
         }
         float s[L1][npl][2];
 #pragma unroll
@@ -451,11 +467,11 @@ __global__ void __launch_bounds__(256) autocorr_lag_kernel(const int32_t* __rest
             float2 xa[K], xb[K], ya[K], yb[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                xa[k] = t[(uy + ddy) * K + k];
-                xb[k] = t[uy * K + k];
+                xa[k] = times(t[(uy + ddy) * K + k], tx);
+                xb[k] = times(t[uy * K + k], tx);
                 if constexpr (P == 2) {
-                    ya[k] = t[K * K + (uy + ddy) * K + k];
-                    yb[k] = t[K * K + uy * K + k];
+                    ya[k] = times(t[K * K + (uy + ddy) * K + k], ty);
+                    yb[k] = times(t[K * K + uy * K + k], ty);
                 }
             }
 #pragma unroll

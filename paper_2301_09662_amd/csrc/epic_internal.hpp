@@ -102,7 +102,7 @@ struct SubDev {
     int pair_wd = 0;                  // compiled window size
     // its gather program, in slices of 64 cells whose groups lie side by side
     int pair_gmax = 0;                // largest group count over channels
-    ChanInfo* pair_chans = nullptr;
+    ChanInfo* pair_chans = nullptr;   // grp_off in units of 64 groups
     CellDesc* pair_desc = nullptr;    // x: operand offset | groups of the slice << 16, y: first group of the slice
     uint16_t* pair_ant = nullptr;
     uint8_t* pair_tap = nullptr;

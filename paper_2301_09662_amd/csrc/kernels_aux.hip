@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(256) weights_kernel(GatherProgram plain, int n
         const CellDesc d = sliced.desc[ci.cell_off + 64 * b + lane];
         for (int j = wv; j < (int)(d.x >> 16); j += 4) {
             // a group's indices, then all its taps and gains: two round trips
-            const int64_t ge = ((int64_t)ci.grp_off + d.y + 64 * j + lane) * kGroup;
+            const int64_t ge = (64 * (int64_t)ci.grp_off + d.y + 64 * j + lane) * kGroup;
             const ushort4 an = *reinterpret_cast<const ushort4*>(sliced.ant + ge);
             const uchar4 tp = *reinterpret_cast<const uchar4*>(sliced.tap + ge);
             const int aa[4] = {an.x, an.y, an.z, an.w}, tt[4] = {tp.x, tp.y, tp.z, tp.w};

@@ -441,8 +441,8 @@ __attribute__((amdgpu_waves_per_eu(pair_waves<PairShape<N_, WD_, SPLIT, P>>())))
         const int R4 = (ci.R + 3) & ~3;
         const int M1 = P * R4;
         const CellDesc* g_desc = a.desc + ci.cell_off;
-        const uint2* g_ant = a.grp_ant + ci.grp_off;
-        const float4* g_w = a.grp_w + (int64_t)ci.grp_off * GF4;
+        const uint2* g_ant = a.grp_ant + 64 * (int64_t)ci.grp_off;
+        const float4* g_w = a.grp_w + 64 * (int64_t)ci.grp_off * GF4;
         // with products of three steps and more, registers are too few to keep
         // what a lane number gives in this segment's loads over the whole kernel
         // (N = 192, 44 x 44 cells, both pols: 720 us with, 509 without; station,

@@ -310,7 +310,7 @@ void build_slices(SubHost& h, uint32_t pitch) {
         const ChanInfo& ci = h.chans[c];
         ChanInfo& pi = h.pair_chans[c];
         pi.cell_off = (int32_t)n_desc;
-        pi.grp_off = (int32_t)n_grp;
+        pi.grp_off = (int32_t)(n_grp / 64);   // of slices: padding may take the groups past 2^31
         uint32_t g = 0;
         for (int k = 0; k < ci.n_cell; k += 64) g += 64 * (h.cells_desc[ci.cell_off + k].x >> 16);
         pi.n_grp = (int32_t)g;
@@ -335,7 +335,7 @@ void build_slices(SubHost& h, uint32_t pitch) {
             for (int l = 0; l < nc; ++l)
                 for (uint32_t j = 0; j < (cd[l].x >> 16); ++j) {
                     const size_t src = ((size_t)ci.grp_off + cd[l].y + j) * kGroup;
-                    const size_t dst = ((size_t)pi.grp_off + g + 64 * j + l) * kGroup;
+                    const size_t dst = (64 * (size_t)pi.grp_off + g + 64 * j + l) * kGroup;
                     std::memcpy(&h.pair_ant[dst], &h.grp_ant[src], kGroup * sizeof(uint16_t));
                     std::memcpy(&h.pair_tap[dst], &h.grp_tap[src], kGroup);
                 }
@@ -1341,7 +1341,7 @@ epic_status make_plan(const epic_plan_desc* desc, hipStream_t st, epic_plan_s* p
             ar.add(&d.pair_desc, h.pair_desc);
             ar.add(&d.pair_ant, h.pair_ant);
             ar.add(&d.pair_tap, h.pair_tap);
-            ar.add(&d.pair_w, h.pair_ant.size() * 2 * (size_t)d.P);
+            ar.add(&d.pair_w, h.pair_ant.size() * group_f4_of(d.P, d.wmode));   // 4 floats a group of 4 entries
             ar.add(&pair_dft, (size_t)pair_table_halfs(d));
             if (d.precision == EPIC_FP32) {
                 ar.add(&d.row_top, h.row_top);

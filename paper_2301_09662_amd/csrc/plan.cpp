@@ -72,6 +72,7 @@ struct SubHost {
     std::vector<ChanInfo> chans;     // [C]
     std::vector<CellDesc> cells_desc;
     // the same program in slices of 64 cells (paired-transform kernel)
+    int64_t sliced_cells = 0, sliced_groups = 0;   // its length over all channels
     std::vector<ChanInfo> pair_chans;
     std::vector<CellDesc> pair_desc;
     std::vector<uint16_t> pair_ant;
@@ -210,6 +211,7 @@ epic_status geometry(SubHost& h) {
 void build_gather(SubHost& h) {
     const epic_array_desc& s = h.desc;
     const int A = s.n_ant, C = s.n_chan, K = s.kernel_k, hk = K / 2;
+    h.sliced_cells = h.sliced_groups = 0;
     h.chans.assign(C, ChanInfo{});
     h.row_top.assign(C, 0);
     int Rmax = 0, Wmax = 0;
@@ -286,6 +288,8 @@ void build_gather(SubHost& h) {
         int sliced = 0;   // groups of the same program in slices of 64 cells (build_slices)
         for (int k = 0; k < ci.n_cell; k += 64) sliced += 64 * (int)(h.cells_desc[ci.cell_off + k].x >> 16);
         SlicedMax = std::max(SlicedMax, sliced);
+        h.sliced_cells += (ci.n_cell + 63) / 64 * 64;
+        h.sliced_groups += sliced;
     }
     h.dev.Gmax = Gmax; h.dev.CellMax = CellMax; h.dev.pair_gmax = SlicedMax;
     int r4 = 0, w4 = 0;
@@ -507,6 +511,11 @@ struct Arena {
         *dst = nullptr;
         if (bytes) items.push_back({dst, bytes, 0, src});
     }
+    size_t bytes() const {
+        size_t n = 0;
+        for (const Item& it : items) n += (it.bytes + 255) & ~(size_t)255;
+        return n;
+    }
     epic_status commit(epic_plan_s* p, hipStream_t st) {
         for (int with_src = 1; with_src >= 0; --with_src)
             for (Item& it : items)
@@ -528,6 +537,81 @@ struct Arena {
         return hip_status(hipMemcpyAsync(base, host.data(), n_src, hipMemcpyHostToDevice, st));
     }
 };
+
+// The tables of a sub-array on the device, for their allocation and for the
+// byte count of a dry run (which builds no sliced program: its size is known).
+struct Tables {
+    bool dft, direct, gemm;
+    size_t bg_bytes, n_vaa, n_lag;
+};
+
+Tables list_tables(const epic_plan_s* p, SubHost& h, Arena& ar) {
+    SubDev& d = h.dev;
+    Tables t{};
+    // the plain gather program serves the vector and E-field kernels, the
+    // batched launch and the GEMM forms' weights
+    const bool plain = d.precision == EPIC_FP32 || d.gridder != EPIC_GRID_GATHER || h.tune || p->can_batch;
+    t.gemm = d.gridder == EPIC_GRID_DENSE_GEMM || d.gridder == EPIC_GRID_BLOCK_GEMM || h.tune;
+    t.dft = d.precision != EPIC_FP32 && d.KK > 0 && d.KK <= 4 && plain;   // grid-and-FFT forms
+    t.direct = d.gridder == EPIC_GRID_DIRECT_GEMM;
+    for (const SubDev& c : h.cands) t.direct = t.direct || c.gridder == EPIC_GRID_DIRECT_GEMM;
+    ar.add(&d.chans, h.chans);
+    ar.add(&d.cells, h.cells);
+    ar.add(&d.gfrac, h.gfrac);
+    if (plain) {
+        ar.add(&d.cells_desc, h.cells_desc);
+        ar.add(&d.grp_ant, h.grp_ant);
+        ar.add(&d.grp_tap, h.grp_tap);
+        ar.add(&d.grp_w, h.grp_ant.size() * 2 * (size_t)d.P);
+    }
+    if (!h.user_taps.empty()) ar.add(&d.taps, h.user_taps);
+    else ar.add(&d.taps, (size_t)d.C * d.A * d.P * d.K * d.K * 2);
+    ar.add(&d.twiddle, (size_t)d.N);
+    if (t.dft) ar.put(&d.dft16, (size_t)2 * d.N * 32 * d.KK * sizeof(uint16_t), nullptr);
+    if (d.pair) {
+        const size_t n_desc = (size_t)h.sliced_cells, n_entry = (size_t)h.sliced_groups * kGroup;
+        if (p->dry_run) {
+            ar.add(&d.pair_chans, (size_t)d.C);
+            ar.add(&d.pair_desc, n_desc);
+            ar.add(&d.pair_ant, n_entry);
+            ar.add(&d.pair_tap, n_entry);
+        } else {
+            build_slices(h, (uint32_t)pair_pitch(d));
+            ar.add(&d.pair_chans, h.pair_chans);
+            ar.add(&d.pair_desc, h.pair_desc);
+            ar.add(&d.pair_ant, h.pair_ant);
+            ar.add(&d.pair_tap, h.pair_tap);
+        }
+        ar.add(&d.pair_w, n_entry * group_f4_of(d.P, d.wmode));   // 4 floats a group of 4 entries
+        ar.put(&d.pair_dft, (size_t)pair_table_halfs(d) * sizeof(uint16_t), nullptr);
+        if (d.precision == EPIC_FP32) {
+            ar.add(&d.row_top, h.row_top);
+            ar.add(&d.row_bound, (size_t)d.C * kRowBounds * d.P);
+            ar.add(&d.peak, (size_t)d.C * d.A * d.P);
+            ar.add(&d.range, (size_t)2 * d.C * kRowBounds * d.P);
+            ar.add(&d.uneven, (size_t)2 * d.C);
+        }
+    }
+    if (t.direct) ar.put(&d.dir_m, (size_t)direct_matrix_halfs(d) * sizeof(uint16_t), nullptr);
+    d.bg_nterm = d.precision == EPIC_FP8 ? 3 : 2;
+    t.bg_bytes = (size_t)h.bg_entries() * 512 * (d.precision == EPIC_FP8 ? 1 : 2) * d.bg_nterm;
+    if (t.gemm) {
+        ar.add(&d.bg_waves, h.bg_waves);
+        ar.add(&d.bg_desc, h.bg_desc);
+        ar.add(&d.bg_dst_ent, h.bg_dst_ent);
+        ar.add(&d.bg_dst_el, h.bg_dst_el);
+        ar.add(&d.bg_w, t.bg_bytes);
+        ar.add(&d.bg_scale, (size_t)2);
+    }
+    t.n_vaa = (size_t)d.C * d.A * (d.P == 2 ? 4 : 1);
+    t.n_lag = (size_t)d.C * (2 * d.K - 1) * (2 * d.K - 1) * (d.P == 2 ? 3 : 1) * 2;
+    if (p->desc.flags & EPIC_F_REMOVE_AUTOCORR) {
+        ar.add(&d.vaa, t.n_vaa);
+        ar.add(&d.lag, t.n_lag);
+        ar.add(&d.lag_total, t.n_lag);
+    }
+    return t;
+}
 
 void free_all(epic_plan_s* p) {
     if (!p->dry_run) {
@@ -1303,80 +1387,24 @@ epic_status make_plan(const epic_plan_desc* desc, hipStream_t st, epic_plan_s* p
     if (p->dry_run) {
         for (SubHost& h : p->subs) {
             const SubDev& d = h.dev;
-            p->device_bytes += (int64_t)d.S * d.C * d.NPP * d.N * d.N * 4 + (int64_t)h.grp_ant.size() * (2 + 1 + 8 * d.P) +
-                               (int64_t)h.cells_desc.size() * 8 + (int64_t)d.C * d.A * d.P * d.K * d.K * 8 +
-                               h.bg_entries() * 512 * (d.precision == EPIC_FP8 ? 3 : 4);
+            Arena ar;
+            (void)list_tables(p, h, ar);
+            p->device_bytes += (int64_t)ar.bytes() + (int64_t)d.S * d.C * d.NPP * d.N * d.N * 4;
         }
+        if (p->can_batch) p->device_bytes += (int64_t)(p->subs.size() * sizeof(BatchSub));
         return EPIC_OK;
     }
     for (SubHost& h : p->subs) {
         SubDev& d = h.dev;
         epic_status s;
-        // the plain gather program serves the vector and E-field kernels, the
-        // batched launch and the GEMM forms' weights
-        const bool plain = d.precision == EPIC_FP32 || d.gridder != EPIC_GRID_GATHER || h.tune || p->can_batch;
-        const bool gemm_tables =
-            d.gridder == EPIC_GRID_DENSE_GEMM || d.gridder == EPIC_GRID_BLOCK_GEMM || h.tune;
-        const bool dft = d.precision != EPIC_FP32 && d.KK > 0 && d.KK <= 4 && plain;   // grid-and-FFT forms
-        bool need_dir = d.gridder == EPIC_GRID_DIRECT_GEMM;
-        for (const SubDev& c : h.cands) need_dir = need_dir || c.gridder == EPIC_GRID_DIRECT_GEMM;
         Arena ar;
-        ar.add(&d.chans, h.chans);
-        ar.add(&d.cells, h.cells);
-        ar.add(&d.gfrac, h.gfrac);
-        if (plain) {
-            ar.add(&d.cells_desc, h.cells_desc);
-            ar.add(&d.grp_ant, h.grp_ant);
-            ar.add(&d.grp_tap, h.grp_tap);
-            ar.add(&d.grp_w, h.grp_ant.size() * 2 * (size_t)d.P);
-        }
-        if (!h.user_taps.empty()) ar.add(&d.taps, h.user_taps);
-        else ar.add(&d.taps, (size_t)d.C * d.A * d.P * d.K * d.K * 2);
-        ar.add(&d.twiddle, (size_t)d.N);
-        uint16_t *dft16 = nullptr, *pair_dft = nullptr, *dir_m = nullptr;
-        if (dft) ar.add(&dft16, (size_t)2 * d.N * 32 * d.KK);
-        if (d.pair) {
-            build_slices(h, (uint32_t)pair_pitch(d));
-            ar.add(&d.pair_chans, h.pair_chans);
-            ar.add(&d.pair_desc, h.pair_desc);
-            ar.add(&d.pair_ant, h.pair_ant);
-            ar.add(&d.pair_tap, h.pair_tap);
-            ar.add(&d.pair_w, h.pair_ant.size() * group_f4_of(d.P, d.wmode));   // 4 floats a group of 4 entries
-            ar.add(&pair_dft, (size_t)pair_table_halfs(d));
-            if (d.precision == EPIC_FP32) {
-                ar.add(&d.row_top, h.row_top);
-                ar.add(&d.row_bound, (size_t)d.C * kRowBounds * d.P);
-                ar.add(&d.peak, (size_t)d.C * d.A * d.P);
-                ar.add(&d.range, (size_t)2 * d.C * kRowBounds * d.P);
-                ar.add(&d.uneven, (size_t)2 * d.C);
-                set_tap_peaks(h);
-                h.uneven = weights_uneven(h, nullptr);
-            }
-        }
-        if (need_dir) ar.add(&dir_m, (size_t)direct_matrix_halfs(d));
-        d.bg_nterm = d.precision == EPIC_FP8 ? 3 : 2;
-        const size_t wbytes = (size_t)h.bg_entries() * 512 * (d.precision == EPIC_FP8 ? 1 : 2) * d.bg_nterm;
-        if (gemm_tables) {
-            ar.add(&d.bg_waves, h.bg_waves);
-            ar.add(&d.bg_desc, h.bg_desc);
-            ar.add(&d.bg_dst_ent, h.bg_dst_ent);
-            ar.add(&d.bg_dst_el, h.bg_dst_el);
-            ar.add(&d.bg_w, wbytes);
-            ar.add(&d.bg_scale, (size_t)2);
-        }
-        const bool ac = (desc->flags & EPIC_F_REMOVE_AUTOCORR) != 0;
-        const size_t nv = (size_t)d.C * d.A * (d.P == 2 ? 4 : 1);
-        const size_t nl = (size_t)d.C * (2 * d.K - 1) * (2 * d.K - 1) * (d.P == 2 ? 3 : 1) * 2;
-        if (ac) {
-            ar.add(&d.vaa, nv);
-            ar.add(&d.lag, nl);
-            ar.add(&d.lag_total, nl);
-        }
+        const Tables tb = list_tables(p, h, ar);
         if ((s = ar.commit(p, st)) != EPIC_OK) return s;
-        d.dft16 = dft16;
-        d.pair_dft = pair_dft;
-        d.dir_m = dir_m;
         d.gains = nullptr;
+        if (d.range) {
+            set_tap_peaks(h);
+            h.uneven = weights_uneven(h, nullptr);
+        }
         const size_t nslot = (size_t)d.S * d.C * d.NPP * d.N * d.N;
         if ((s = dalloc(p, &d.slots, nslot)) != EPIC_OK) return s;
         if ((s = hip_status(hipMemsetAsync(d.slots, 0, nslot * sizeof(float), st))) != EPIC_OK) return s;
@@ -1385,18 +1413,18 @@ epic_status make_plan(const epic_plan_desc* desc, hipStream_t st, epic_plan_s* p
                  d, h.desc.kernel_sigma_cells > 0.0 ? h.desc.kernel_sigma_cells : 0.5, st))) != EPIC_OK)
             return s;
         if ((s = hip_status(launch_twiddles(d, st))) != EPIC_OK) return s;
-        if (dft && (s = hip_status(launch_dft_matrix(d, st))) != EPIC_OK) return s;
+        if (tb.dft && (s = hip_status(launch_dft_matrix(d, st))) != EPIC_OK) return s;
         if (d.pair && (s = hip_status(launch_pair_table(d, st))) != EPIC_OK) return s;
         if ((s = hip_status(launch_weights(d, st))) != EPIC_OK) return s;
-        if (need_dir && (s = hip_status(launch_direct_matrix(d, st))) != EPIC_OK) return s;
-        if (gemm_tables) {
-            if ((s = hip_status(hipMemsetAsync(d.bg_w, 0, wbytes, st))) != EPIC_OK) return s;
+        if (tb.direct && (s = hip_status(launch_direct_matrix(d, st))) != EPIC_OK) return s;
+        if (tb.gemm) {
+            if ((s = hip_status(hipMemsetAsync(d.bg_w, 0, tb.bg_bytes, st))) != EPIC_OK) return s;
             if ((s = hip_status(hipMemsetAsync(d.bg_scale, 0, 2 * sizeof(float), st))) != EPIC_OK) return s;
             if ((s = hip_status(launch_bg_weights(d, st))) != EPIC_OK) return s;
         }
-        if (ac) {
-            if ((s = hip_status(hipMemsetAsync(d.vaa, 0, nv * sizeof(float), st))) != EPIC_OK) return s;
-            if ((s = hip_status(hipMemsetAsync(d.lag, 0, nl * sizeof(float), st))) != EPIC_OK) return s;
+        if (d.vaa) {
+            if ((s = hip_status(hipMemsetAsync(d.vaa, 0, tb.n_vaa * sizeof(float), st))) != EPIC_OK) return s;
+            if ((s = hip_status(hipMemsetAsync(d.lag, 0, tb.n_lag * sizeof(float), st))) != EPIC_OK) return s;
         }
     }
     // autotuner: each sub-array's launch candidates timed (or their choice taken

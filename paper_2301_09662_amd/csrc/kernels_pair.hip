@@ -933,6 +933,19 @@ hipError_t pair_configure(SubDev& d, int device, int num_cu, int force_prog) {
         int blocks = 0;
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, fn, s.TH, L.total);
         if (e != hipSuccess) return e;
+        // Workgroups of six or nine waves are counted as if their waves filled the
+        // SIMDs' slots evenly; what runs side by side is what fits with the odd
+        // waves on the same SIMDs.  The rest would wait for a second round of the
+        // persistent launch (N = 48, single pol, 18 x 18 cells, 16 channels x 301
+        // spectra: 39.8 us for the three counted, 29.8 for two; N = 96, 8 x 8 cells,
+        // 1000 antennas: 355 us for two, 164 for one).
+        const int waves = s.TH / 64;
+        if (waves > 4 && waves % 4 != 0) {
+            hipFuncAttributes at{};
+            if ((e = hipFuncGetAttributes(&at, fn)) != hipSuccess) return e;
+            const int slots = std::min(8, 512 / ((std::max(at.numRegs, 1) + 7) / 8 * 8));   // waves per SIMD
+            blocks = std::min(blocks, slots / ((waves + 3) / 4));
+        }
         occ[pl] = blocks > 0 ? blocks : 1;
     }
     // the program in LDS unless that costs a resident workgroup

@@ -72,22 +72,34 @@ namespace epic {
 
 namespace {
 
-constexpr int pair_ks(int N, bool split) { return N <= 64 ? 1 : (N <= 128 ? 2 : (N == 192 && !split ? 4 : 8)); }
+// FP16, N = 192, both pols, windows beyond 32 cells (products of two steps): six
+// column parts of two column tiles each, gathered six times instead of four but
+// with shared products (62 antennas, 16 channels x 200 spectra, 38 x 38 cells:
+// 148 us; half-split, below, 248; unpaired rows 168.  1002 antennas, 62 x 62
+// cells: 294, 332 and 330).
+constexpr bool pair_six(int N, bool split, int P, int WD) { return N == 192 && !split && P == 2 && WD > 32; }
+
+constexpr int pair_ks(int N, bool split, int P, int WD) {
+    return N <= 64 ? 1 : (N <= 128 ? 2 : (pair_six(N, split, P, WD) ? 6 : (N == 192 && !split ? 4 : 8)));
+}
 // Column tiles per wave.  FP16 single-pol grids of 48 and 96 have three column
 // tiles and few registers: all three in one wave make workgroups of two or three
 // waves, several to a CU, whose barriers overlap (station, 4 channels x 1000
 // spectra: N = 96 50.1 -> 35.8 us, N = 48 30.2 -> 23.9; unpaired rows 40.2, 23.4).
-constexpr int pair_itw(int N, bool split, int P) {
+constexpr int pair_itw(int N, bool split, int P, int WD) {
+    if (pair_six(N, split, P, WD)) return 1;
     if (!split && P == 1 && (N == 48 || N == 96)) return 3;
     return N == 128 || (N == 192 && !split) || (N == 256 && split) ? 2 : 1;
 }
 
-// FP16, N = 192, both pols: twelve waves of at most 168 registers.  With the
+// The narrower windows there: twelve waves of at most 168 registers.  With the
 // column tiles split (two tiles and one, 64 accumulators) 40 to 90 registers
 // spill; with each wave computing one output of every pair (chained, twice the
 // products, 48 accumulators) none do: 215 against 139 us for 4 channels x 1000
 // spectra of the station (unpaired rows took 155).
-constexpr bool pair_half(int N, bool split, int P) { return N == 192 && !split && P == 2; }
+constexpr bool pair_half(int N, bool split, int P, int WD) {
+    return N == 192 && !split && P == 2 && !pair_six(N, split, P, WD);
+}
 
 template <int N_, int WD_, bool SPLIT_, int P_ = 2>
 struct PairShape {
@@ -96,7 +108,7 @@ struct PairShape {
     static constexpr bool SPLIT = SPLIT_;
     static constexpr int NH = N / 2;                // pairs
     static constexpr int JT = (NH + 15) / 16;       // tiles of 16 row pairs
-    static constexpr int KS = pair_ks(N, SPLIT);    // workgroups sharing a spectrum's columns
+    static constexpr int KS = pair_ks(N, SPLIT, P_, WD);    // workgroups sharing a spectrum's columns
     static constexpr int NK = N / KS;               // columns per workgroup: NK / 2 pairs
     static constexpr int NKH = NK / 2;
     static constexpr int NIT = (NKH + 15) / 16;     // column-pair tiles of the row pass
@@ -104,8 +116,8 @@ struct PairShape {
     static constexpr int NKP = 16 * NCT;            // columns held in LDS
     // half-split: two waves share a row-pair tile by outputs, rows j and rows
     // N - j, and take every column tile (see pair_half)
-    static constexpr bool HS = pair_half(N, SPLIT, P_);
-    static constexpr int ITW = HS ? NCT : pair_itw(N, SPLIT, P_);   // column tiles per wave
+    static constexpr bool HS = pair_half(N, SPLIT, P_, WD);
+    static constexpr int ITW = HS ? NCT : pair_itw(N, SPLIT, P_, WD);   // column tiles per wave
     static constexpr int CG = HS ? 2 : (NCT + ITW - 1) / ITW;   // column groups (half-split: the halves)
     static constexpr int WAVES = JT * CG;
     static constexpr int TH = 64 * WAVES;
@@ -130,9 +142,6 @@ struct PairShape {
     static_assert((SPLIT ? WD % 4 : WD % 8) == 0 && WAVES <= 16, "");
     static_assert(!SHARE || (NIT == JT && WAVES % NIT == 0), "row-pass tile = column-pass tile");
 };
-
-template <int N, bool SPLIT, int P>
-constexpr int pair_threads_of() { return PairShape<N, 8, SPLIT, P>::TH; }   // the same for every window
 
 // Register budget (waves per SIMD).
 template <class Sh>
@@ -304,7 +313,7 @@ __device__ __forceinline__ void pair_gather(const unsigned char* smem, const Pai
 }
 
 template <int N_, int WD_, int P, int WM, bool SPLIT, bool PROG>
-__global__ void __launch_bounds__((pair_threads_of<N_, SPLIT, P>()))
+__global__ void __launch_bounds__((PairShape<N_, WD_, SPLIT, P>::TH))
 __attribute__((amdgpu_waves_per_eu(pair_waves<PairShape<N_, WD_, SPLIT, P>>()))) pair_kernel(PairArgs a) {
     using Sh = PairShape<N_, WD_, SPLIT, P>;
     constexpr int N = Sh::N, WD = Sh::WD, SD = Sh::SD, PITCH = Sh::PITCH, ST = Sh::ST, NK = Sh::NK, NKH = Sh::NKH, NKP = Sh::NKP;
@@ -770,11 +779,11 @@ PairDims pair_dims(int N, int WD, bool split, int P) {
     d.SD = split ? 2 * WD : WD;
     d.ST = ((split ? 3 * WD : WD) + 31) / 32;
     d.PITCH = ((2 * d.SD / 8) | 1) * 8;
-    const bool hs = pair_half(N, split, P);
-    d.PL = (pair_ks(N, split) == 1 && d.ST == 1) || hs ? 4 : 2;
-    d.KS = pair_ks(N, split);
+    const bool hs = pair_half(N, split, P, WD);
+    d.PL = (pair_ks(N, split, P, WD) == 1 && d.ST == 1) || hs ? 4 : 2;
+    d.KS = pair_ks(N, split, P, WD);
     const int NK = N / d.KS, NCT = (NK + 15) / 16, NIT = (NK / 2 + 15) / 16, JT = (N / 2 + 15) / 16;
-    const int ITW = pair_itw(N, split, P);
+    const int ITW = pair_itw(N, split, P, WD);
     d.NKP = 16 * NCT;
     d.TR = std::max(16 * JT, (d.KS - 1) * (NK / 2) + 16 * NIT);
     d.TH = 64 * JT * (hs ? 2 : (NCT + ITW - 1) / ITW);

@@ -923,6 +923,10 @@ hipError_t pair_configure(SubDev& d, int device, int num_cu, int force_prog) {
     const bool split = d.precision == EPIC_FP32;
     d.pair_wd = pair_wd(std::max(d.R4max, d.W4max), split);
     if (d.pair_wd == 0) return hipErrorNotSupported;
+    // FP32, N = 192, both pols, windows beyond 52 cells: more than 90 of twelve
+    // waves' registers spill (62 antennas, 16 channels x 200 spectra: 834 us, the
+    // vector kernel 735)
+    if (split && d.N == 192 && d.P == 2 && d.pair_wd > 52) return hipErrorNotSupported;
     const PairDims s = pair_dims(d.N, d.pair_wd, split, d.P);
     const PairLayout with = pair_layout(d, true), without = pair_layout(d, false);
     // workgroups per CU with the program in LDS or streamed (device < 0: by LDS only)

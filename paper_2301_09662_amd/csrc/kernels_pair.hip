@@ -452,11 +452,12 @@ __attribute__((amdgpu_waves_per_eu(pair_waves<PairShape<N_, WD_, SPLIT, P>>())))
         const CellDesc* g_desc = a.desc + ci.cell_off;
         const uint2* g_ant = a.grp_ant + 64 * (int64_t)ci.grp_off;
         const float4* g_w = a.grp_w + 64 * (int64_t)ci.grp_off * GF4;
-        // with products of three steps and more, registers are too few to keep
-        // what a lane number gives in this segment's loads over the whole kernel
-        // (N = 192, 44 x 44 cells, both pols: 720 us with, 509 without; station,
+        // with products of three steps and more, or a row-pass operand of its own,
+        // registers are too few to keep what a lane number gives in this segment's
+        // loads over the whole kernel (N = 192, 44 x 44 cells, both pols: 720 us
+        // with, 509 without; N = 96, 8 x 8 cells, 1000 antennas 177 and 152; station,
         // two steps: 564 with, 575 without)
-        const int ls = ST > 2 ? opaque(lane) : lane;
+        const int ls = ST > 2 || !Sh::SHARE ? opaque(lane) : lane;
         // the rows' bounds, a lane each, are loaded here and reduced after the
         // copies below
         float most = 0.f;

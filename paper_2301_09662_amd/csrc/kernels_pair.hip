@@ -791,8 +791,8 @@ PairDims pair_dims(int N, int WD, bool split, int P) {
     return d;
 }
 
-// Window sizes compiled per form: the largest of each count of MFMA steps.
-// (The FP16 form's two-step sizes differ in LDS.)
+// Window sizes compiled per form: FP32, the largest of each count of MFMA steps;
+// FP16, 16 to 32 (one step) and 48, 64 (two), which differ in LDS.
 int pair_wd(int need, bool split) {
     if (split) {
         for (int w : {8, 20, 32, 40, 52, 64})
@@ -834,11 +834,20 @@ PairLayout pair_layout(const SubDev& d, bool prog) {
 
 using KernelFn = void (*)(PairArgs);
 
+// FP32, N = 192, both pols, windows beyond 52 cells: more than 90 of twelve waves'
+// registers spill (62 antennas, 16 channels x 200 spectra: 834 us, the vector
+// kernel 735), so there are no such instances.
+constexpr bool pair_spills(int N, bool split, int P, int WD) { return split && N == 192 && P == 2 && WD > 52; }
+
 template <int N, int WD, bool SPLIT, bool PROG>
 KernelFn pair_pick2(int P, int wm) {
     if (P == 2) {
-        if (wm == kWComplex) return pair_kernel<N, WD, 2, kWComplex, SPLIT, PROG>;
-        return wm == kWShared ? pair_kernel<N, WD, 2, kWShared, SPLIT, PROG> : pair_kernel<N, WD, 2, kWReal, SPLIT, PROG>;
+        if constexpr (pair_spills(N, SPLIT, 2, WD)) {
+            return nullptr;
+        } else {
+            if (wm == kWComplex) return pair_kernel<N, WD, 2, kWComplex, SPLIT, PROG>;
+            return wm == kWShared ? pair_kernel<N, WD, 2, kWShared, SPLIT, PROG> : pair_kernel<N, WD, 2, kWReal, SPLIT, PROG>;
+        }
     }
     return wm == kWComplex ? pair_kernel<N, WD, 1, kWComplex, SPLIT, PROG> : pair_kernel<N, WD, 1, kWReal, SPLIT, PROG>;
 }
@@ -854,19 +863,16 @@ constexpr size_t kLdsLimit = 160 * 1024;
 
 // The instances are spread over several translation units of this file, each
 // compiled with EPIC_PAIR_UNIT = 0, 1, ...; unit 0 also holds the host side.
-#define EPIC_PAIR_SPLIT6(NN) \
-    case NN * 64 + 8: return pair_pick<NN, 8, true>(P, wm, prog);   \
-    case NN * 64 + 20: return pair_pick<NN, 20, true>(P, wm, prog); \
-    case NN * 64 + 32: return pair_pick<NN, 32, true>(P, wm, prog); \
-    case NN * 64 + 40: return pair_pick<NN, 40, true>(P, wm, prog); \
-    case NN * 64 + 52: return pair_pick<NN, 52, true>(P, wm, prog); \
-    case NN * 64 + 63: return pair_pick<NN, 64, true>(P, wm, prog);
-#define EPIC_PAIR_HALF5(NN)                                           \
-    case NN * 64 + 16: return pair_pick<NN, 16, false>(P, wm, prog); \
-    case NN * 64 + 24: return pair_pick<NN, 24, false>(P, wm, prog); \
-    case NN * 64 + 32: return pair_pick<NN, 32, false>(P, wm, prog); \
-    case NN * 64 + 48: return pair_pick<NN, 48, false>(P, wm, prog); \
-    case NN * 64 + 63: return pair_pick<NN, 64, false>(P, wm, prog);
+// A grid holds windows up to its own side, in the smallest compiled size that
+// fits them: 32 at N = 32, FP32 52 and FP16 48 at N = 48.
+#define EPIC_PAIR_CASE(NN, WD, SPLIT) \
+    case NN * 64 + (WD == 64 ? 63 : WD): return pair_pick<NN, WD, SPLIT>(P, wm, prog);
+#define EPIC_PAIR_SPLIT32(NN) EPIC_PAIR_CASE(NN, 8, true) EPIC_PAIR_CASE(NN, 20, true) EPIC_PAIR_CASE(NN, 32, true)
+#define EPIC_PAIR_SPLIT52(NN) EPIC_PAIR_SPLIT32(NN) EPIC_PAIR_CASE(NN, 40, true) EPIC_PAIR_CASE(NN, 52, true)
+#define EPIC_PAIR_SPLIT64(NN) EPIC_PAIR_SPLIT52(NN) EPIC_PAIR_CASE(NN, 64, true)
+#define EPIC_PAIR_HALF32(NN) EPIC_PAIR_CASE(NN, 16, false) EPIC_PAIR_CASE(NN, 24, false) EPIC_PAIR_CASE(NN, 32, false)
+#define EPIC_PAIR_HALF48(NN) EPIC_PAIR_HALF32(NN) EPIC_PAIR_CASE(NN, 48, false)
+#define EPIC_PAIR_HALF64(NN) EPIC_PAIR_HALF48(NN) EPIC_PAIR_CASE(NN, 64, false)
 
 #define EPIC_PAIR_SELECT(NAME, CASES)                       \
     void* NAME(int key, int P, int wm, bool prog) {         \
@@ -875,21 +881,21 @@ constexpr size_t kLdsLimit = 160 * 1024;
     }
 
 #if EPIC_PAIR_UNIT == 0
-EPIC_PAIR_SELECT(pair_select_split_32, EPIC_PAIR_SPLIT6(32) EPIC_PAIR_SPLIT6(48))
+EPIC_PAIR_SELECT(pair_select_split_32, EPIC_PAIR_SPLIT32(32) EPIC_PAIR_SPLIT52(48))
 #elif EPIC_PAIR_UNIT == 1
-EPIC_PAIR_SELECT(pair_select_split_64, EPIC_PAIR_SPLIT6(64))
+EPIC_PAIR_SELECT(pair_select_split_64, EPIC_PAIR_SPLIT64(64))
 #elif EPIC_PAIR_UNIT == 2
-EPIC_PAIR_SELECT(pair_select_split_96, EPIC_PAIR_SPLIT6(96))
+EPIC_PAIR_SELECT(pair_select_split_96, EPIC_PAIR_SPLIT64(96))
 #elif EPIC_PAIR_UNIT == 3
-EPIC_PAIR_SELECT(pair_select_split_128, EPIC_PAIR_SPLIT6(128))
+EPIC_PAIR_SELECT(pair_select_split_128, EPIC_PAIR_SPLIT64(128))
 #elif EPIC_PAIR_UNIT == 4
-EPIC_PAIR_SELECT(pair_select_split_192, EPIC_PAIR_SPLIT6(192))
+EPIC_PAIR_SELECT(pair_select_split_192, EPIC_PAIR_SPLIT64(192))
 #elif EPIC_PAIR_UNIT == 5
-EPIC_PAIR_SELECT(pair_select_split_256, EPIC_PAIR_SPLIT6(256))
+EPIC_PAIR_SELECT(pair_select_split_256, EPIC_PAIR_SPLIT64(256))
 #elif EPIC_PAIR_UNIT == 6
-EPIC_PAIR_SELECT(pair_select_half_small, EPIC_PAIR_HALF5(32) EPIC_PAIR_HALF5(48) EPIC_PAIR_HALF5(64))
+EPIC_PAIR_SELECT(pair_select_half_small, EPIC_PAIR_HALF32(32) EPIC_PAIR_HALF48(48) EPIC_PAIR_HALF64(64))
 #elif EPIC_PAIR_UNIT == 7
-EPIC_PAIR_SELECT(pair_select_half_large, EPIC_PAIR_HALF5(96) EPIC_PAIR_HALF5(128) EPIC_PAIR_HALF5(192) EPIC_PAIR_HALF5(256))
+EPIC_PAIR_SELECT(pair_select_half_large, EPIC_PAIR_HALF64(96) EPIC_PAIR_HALF64(128) EPIC_PAIR_HALF64(192) EPIC_PAIR_HALF64(256))
 #endif
 
 #if EPIC_PAIR_UNIT == 0
@@ -916,18 +922,15 @@ const void* pair_select(const SubDev& d) {
 }  // namespace
 
 // Launch shape: grids of 32..128 (multiples of 16, not 80 / 112), 192 and 256
-// with windows of at most 64 cells; the gather program in LDS when that leaves
-// room for two workgroups per CU, else streamed from L2.
+// with windows of at most 64 cells whose operands fit LDS; the gather program in
+// LDS unless that costs a resident workgroup, else streamed from L2.
 hipError_t pair_configure(SubDev& d, int device, int num_cu, int force_prog) {
     const bool grid_ok = d.N == 32 || d.N == 48 || d.N == 64 || d.N == 96 || d.N == 128 || d.N == 192 || d.N == 256;
     if (!grid_ok) return hipErrorNotSupported;
     const bool split = d.precision == EPIC_FP32;
     d.pair_wd = pair_wd(std::max(d.R4max, d.W4max), split);
     if (d.pair_wd == 0) return hipErrorNotSupported;
-    // FP32, N = 192, both pols, windows beyond 52 cells: more than 90 of twelve
-    // waves' registers spill (62 antennas, 16 channels x 200 spectra: 834 us, the
-    // vector kernel 735)
-    if (split && d.N == 192 && d.P == 2 && d.pair_wd > 52) return hipErrorNotSupported;
+    if (pair_spills(d.N, split, d.P, d.pair_wd)) return hipErrorNotSupported;
     const PairDims s = pair_dims(d.N, d.pair_wd, split, d.P);
     const PairLayout with = pair_layout(d, true), without = pair_layout(d, false);
     // workgroups per CU with the program in LDS or streamed (device < 0: by LDS only)

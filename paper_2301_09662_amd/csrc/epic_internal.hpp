@@ -206,7 +206,7 @@ hipError_t launch_pair_table(const SubDev& d, hipStream_t st);
 hipError_t launch_pair(const SubDev& d, const uint8_t* samples, int64_t n_time, hipStream_t st);
 
 // Gridding on the matrix cores (kernels_bgemm.hip): launch shape, the split
-// operand weights (after launch_entry_weights), and the hot path.
+// operand weights (after launch_weights), and the hot path.
 // force_tb: 0 library choice, else that many spectra per gridding step
 hipError_t bg_configure(SubDev& d, int device, int num_cu, int force_tb = 0);
 hipError_t launch_bg_weights(const SubDev& d, hipStream_t st);

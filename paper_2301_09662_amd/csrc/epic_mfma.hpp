@@ -41,6 +41,9 @@ constexpr int kPadH = 8;
 // on the 16-antenna array).
 constexpr bool own_form(int N, int KK) { return N <= 32 && (N / 16) * KK <= 8; }
 
+// Column parts of the grids that these kernels hold (up to 128).
+constexpr int mfma_ks(int N) { return N <= 64 ? 1 : 2; }
+
 template <int N_, int KK_>
 struct MShape {
     static constexpr int N = N_;
@@ -48,16 +51,14 @@ struct MShape {
     static constexpr int KPAD = 16 * KK;           // window extent padded (cells)
     static constexpr int K2 = 2 * KPAD;            // real-form depth: [re | im]
     // image columns split over KS workgroups: a wave keeps its 16 image rows'
-    // products of NK columns in registers, at most 64 columns, and 32 for the
-    // 16-wave workgroups of N = 256 (whose 128-register budget holds no more)
-    static constexpr int KS = (N <= 64) ? 1 : (N <= 128 ? 2 : (N <= 192 ? 4 : 8));
+    // products of NK columns in registers, at most 64 columns
+    static constexpr int KS = mfma_ks(N);
     static constexpr int NK = N / KS;              // columns per workgroup
     static constexpr int IT = NK / 16;             // 16-column tiles per workgroup
     static constexpr int WAVES = N / 16;           // one wave per 16 image rows
     static constexpr int TILES1 = 2 * NK / 16;     // row-pass output tiles: [Re | Im] of NK columns
-    static constexpr int NT1 = (TILES1 + WAVES - 1) / WAVES;   // row-pass output tiles per wave
-    // waves beyond TILES1 / NT1 (grids above 128) sit the row pass out
-    static constexpr bool ALL_ROW_WAVES = TILES1 == WAVES * NT1;
+    static constexpr int NT1 = TILES1 / WAVES;     // row-pass output tiles per wave
+    static_assert(N <= 128 && TILES1 == WAVES * NT1, "");
     static constexpr bool OWN = own_form(N, KK);
     static constexpr int RT = N / 16;              // image row tiles (column-owner form)
     static constexpr int A1P = K2 + kPadH;         // LDS pitches (halfs)
@@ -91,7 +92,6 @@ __device__ __forceinline__ void load_row_fragments(half8 (&b1)[Sh::NT1][Sh::KK],
                                                    int kpart, int mw, int l16, int l4) {
 #pragma unroll
     for (int u = 0; u < Sh::NT1; ++u) {
-        if (!Sh::ALL_ROW_WAVES && mw * Sh::NT1 + u >= Sh::TILES1) continue;
         const int nloc = 16 * (mw * Sh::NT1 + u) + l16;          // own-column index in [0, 2 NK)
         const int row = (nloc < Sh::NK) ? kpart * Sh::NK + nloc : Sh::N + kpart * Sh::NK + (nloc - Sh::NK);
 #pragma unroll
@@ -119,7 +119,6 @@ __device__ __forceinline__ void row_pass(const _Float16* __restrict__ s_A1, _Flo
         const int m0 = 16 * mt + 4 * l4;
 #pragma unroll
         for (int u = 0; u < NT1; ++u) {
-            if (!Sh::ALL_ROW_WAVES && mw * NT1 + u >= Sh::TILES1) continue;
             floatx4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < KK; ++ks) d = mfma16(af[ks], b1[u][ks], d);

@@ -473,7 +473,7 @@ BgLayout bg_layout(const SubDev& d, int TB) {
     size_t b = 0;
     const int eb = d.precision == EPIC_FP8 ? 1 : 2;
     const int K2 = 32 * d.KK;
-    const int NK = d.N / (d.N > 64 ? 2 : 1);
+    const int NK = d.N / mfma_ks(d.N);
     L.A1rows = TB * d.P * d.R4max + 16;
     // an antenna's row of the field operand: its columns, at least the 8 bytes of one read
     for (L.erow_log2 = 3; (1 << L.erow_log2) < TB * 2 * d.P * eb; ++L.erow_log2) {}
@@ -522,7 +522,7 @@ hipError_t bg_configure(SubDev& d, int device, int num_cu, int force_tb) {
     if (d.N < 32 || d.N > 128 || d.N % 16 != 0 || d.N == 80 || d.N == 112) return hipErrorNotSupported;
     if (d.KK < 1 || 16 * d.KK > d.N || d.KK > 4) return hipErrorNotSupported;
     if (!(d.wmode == kWShared || (d.P == 1 && d.wmode == kWReal))) return hipErrorNotSupported;
-    d.KS = d.N > 64 ? 2 : 1;
+    d.KS = mfma_ks(d.N);
     d.threads = 64 * (d.N / 16);
     const int target = (d.N <= 64 && d.KK <= 2) ? 2 : 1;   // workgroups per CU the registers allow
     const int tbmax = 16 / (2 * d.P);

@@ -71,15 +71,14 @@ __device__ __forceinline__ void gather_cells(DescP desc, AntP gant, WP_ wts, int
 }
 
 // Process the spectra [k0, k1) of a sequence (index s*T + t) of one
-// sub-array with TH threads; sequence channel s is virtual channel
-// v = s * vstep + voff (channel v / KS, column part v % KS).  Waves beyond
+// sub-array with TH threads; sequence channel v is the virtual channel of
+// channel v / KS and column part v % KS.  Waves beyond
 // N/16 only help with the decoding, gathering and clearing.  The spectra's
 // cost offsets are base + k*w in units where workgroup g's share is Lc
 // (slot choice in slot_of).
 template <int N_, int KK_, int P, int WM, int TH>
 __device__ __forceinline__ void mfma_run(const SegCtx& sc, const LdsMap& lm, unsigned char* smem, int64_t T, int g,
-                                         int64_t k0, int64_t k1, int64_t base, int64_t w_cost, int64_t Lc,
-                                         int vstep, int voff) {
+                                         int64_t k0, int64_t k1, int64_t base, int64_t w_cost, int64_t Lc) {
     using Sh = MShape<N_, KK_>;
     constexpr int N = Sh::N, KK = Sh::KK, KPAD = Sh::KPAD, K2 = Sh::K2, KS = Sh::KS, NK = Sh::NK;
     constexpr int IT = Sh::IT, NT1 = Sh::NT1, A1P = Sh::A1P, B2P = Sh::B2P, WAVES = Sh::WAVES;
@@ -153,16 +152,15 @@ __device__ __forceinline__ void mfma_run(const SegCtx& sc, const LdsMap& lm, uns
         }
     };
 
-    int s_ch = (int)(k0 / T);   // sequence channel
-    int64_t t = k0 - (int64_t)s_ch * T;
-    int v = s_ch * vstep + voff;
+    int v = (int)(k0 / T);
+    int64_t t = k0 - (int64_t)v * T;
     if (words) prefetch(v, t);
     for (int64_t f = k0; f < k1;) {
         // one channel segment: spectra t .. t+n-1 of virtual channel v
         const int64_t n = (k1 - f < T - t) ? k1 - f : T - t;
         const int c = v / KS;
         const int kpart = v - c * KS;
-        const int slot = slot_of(g, s_ch, t, T, base, w_cost, Lc);
+        const int slot = slot_of(g, v, t, T, base, w_cost, Lc);
         const ChanInfo ci = sc.chans[c];
         const int n_cell = ci.n_cell;
         const int R4 = (ci.R + 3) & ~3;
@@ -202,7 +200,7 @@ __device__ __forceinline__ void mfma_run(const SegCtx& sc, const LdsMap& lm, uns
         decode(s_smp0, c, t);
         if (words && f + 1 < k1) {
             if (t + 1 < T) prefetch(v, t + 1);
-            else prefetch(v + vstep, 0);
+            else prefetch(v + 1, 0);
         }
         __syncthreads();
 
@@ -229,7 +227,7 @@ __device__ __forceinline__ void mfma_run(const SegCtx& sc, const LdsMap& lm, uns
                 decode(s_nxt, c, tt + 1);
                 if (words && f + i + 2 < k1) {
                     if (tt + 2 < T) prefetch(v, tt + 2);
-                    else prefetch(v + vstep, 0);
+                    else prefetch(v + 1, 0);
                 }
             }
             __syncthreads();
@@ -260,8 +258,7 @@ __device__ __forceinline__ void mfma_run(const SegCtx& sc, const LdsMap& lm, uns
             if (mwave) flush_slot<Sh, P>(sc.slots, slot, sc.C, c, kpart, acc, mw, l16, l4, sc.fresh != 0);
         }
         f += n;
-        ++s_ch;
-        v += vstep;
+        ++v;
         t = 0;
     }
 }
@@ -319,8 +316,8 @@ __global__ void __launch_bounds__(kBatchThreads) batch_kernel(BatchArgs a) {
             sc.nibble_order = bs.nibble_order; sc.prog_lds = bs.prog_lds;
             switch (bs.N * 8 + bs.KK) {
 #define EPIC_RUN(NN, KKK)                                                                           \
-    case NN * 8 + KKK:                                                                              \
-        mfma_run<NN, KKK, P, WM, kBatchThreads>(sc, a.lm, smem, a.T, g, k0, k1, base, w, Lc, 1, 0); \
+    case NN * 8 + KKK:                                                                        \
+        mfma_run<NN, KKK, P, WM, kBatchThreads>(sc, a.lm, smem, a.T, g, k0, k1, base, w, Lc); \
         break;
                 EPIC_BATCH_SHAPES(EPIC_RUN)
 #undef EPIC_RUN
@@ -331,8 +328,6 @@ __global__ void __launch_bounds__(kBatchThreads) batch_kernel(BatchArgs a) {
 }
 
 // ---- launch shapes -----------------------------------------------------------
-int ks_of(int N) { return N <= 64 ? 1 : (N <= 128 ? 2 : (N <= 192 ? 4 : 8)); }
-
 size_t take_aligned(size_t& b, size_t n) {
     b = (b + 15) & ~(size_t)15;
     const size_t o = b;
@@ -353,7 +348,7 @@ size_t a1_bytes(const SubDev& d) {
     return (size_t)(own_form(d.N, d.KK) ? 2 : 1) * m1max_of(d) * (32 * d.KK + kPadH) * 2;
 }
 size_t b2_bytes(const SubDev& d) {
-    return own_form(d.N, d.KK) ? 0 : (size_t)d.P * (d.N / ks_of(d.N)) * (32 * d.KK + kPadH) * 2;
+    return own_form(d.N, d.KK) ? 0 : (size_t)d.P * (d.N / mfma_ks(d.N)) * (32 * d.KK + kPadH) * 2;
 }
 
 using BatchFn = void (*)(BatchArgs);
@@ -420,7 +415,7 @@ hipError_t batch_configure(SubDev* subs, int n_sub, BatchDev& bd, int device, in
         if (d.P != P || d.wmode != wm) return hipErrorNotSupported;
         d.KK = (std::max(d.Rmax, d.Wmax) + 15) / 16;
         if (!batch_shape_ok(d.N, d.KK)) return hipErrorNotSupported;
-        d.KS = ks_of(d.N);
+        d.KS = mfma_ks(d.N);
         const int gf4 = group_f4_of(P, wm);
         gw = std::max(gw, (size_t)d.Gmax * gf4 * 16);
         ga = std::max(ga, (size_t)d.Gmax * 8);

@@ -118,10 +118,12 @@ def mfma_ops_per_spectrum(plan, subs):
     NIT = NK/2/16 and JT = N/2/16 pair tiles, NCT = NK/16 column tiles (each
     rounded up), ST 32-deep steps over the compiled window size (FP32: three
     terms of it), and f = 4, or 8 where both outputs of a pair are chained in
-    the accumulators (KS = ST = 1; FP16 dual pol at N = 192).
+    the accumulators (KS = ST = 1; FP16 dual pol at N = 192 with KS = 4).  FP32
+    plans that run the vector-ALU kernel (`paired_fp32`) execute none.
 
     GEMM-gridding kernel, and the batched launch: ceil(M1/16) x (2 NK/16) x KK
-    and (N/16) x (NK/16) x P x 2 x KK, KK 32-deep steps of [re | im]."""
+    and (N/16) x (NK/16) x P x 2 x KK, KK 32-deep steps of [re | im].  The
+    direct form has no transform passes."""
     from paper_2301_09662_amd import epic as E
     info = E.epic_plan_query(plan)
     split = info["precision"] == 0
@@ -133,16 +135,18 @@ def mfma_ops_per_spectrum(plan, subs):
         W = g[:, :, 0].max(1) - g[:, :, 0].min(1) + 1 + 2 * hk
         N, P = s.grid_n, s.n_pol
         M1 = P * ((R + 3) // 4 * 4)
+        if info["grid_form"][k] == 4:
+            continue
         if info["grid_form"][k] == 1 and not info["batched"]:
             ext = max(-(-int(R.max()) // 4) * 4, -(-int(W.max()) // 4) * 4)
             sizes = (8, 20, 32, 40, 52, 64) if split else (16, 24, 32, 48, 64)
             WD = next((w for w in sizes if w >= ext), None)
-            if WD is None or N in (16, 80, 112):               # the vector-ALU kernel
+            if WD is None or (split and not paired_fp32(s, g, WD)):
                 continue
             KS = info["col_split"][k]
             NK = N // KS
             ST = -(-(3 * WD if split else WD) // 32)
-            f = 8 if (KS == 1 and ST == 1) or (N == 192 and P == 2 and not split) else 4
+            f = 8 if (KS == 1 and ST == 1) or (N == 192 and P == 2 and KS == 4) else 4
             NIT, JT, NCT = -(-NK // 32), -(-N // 32), -(-NK // 16)
             per_c = KS * f * ST * (-(-M1 // 16) * NIT + JT * NCT * P)
         else:
@@ -155,13 +159,42 @@ def mfma_ops_per_spectrum(plan, subs):
     return total
 
 
+def paired_fp32(s, g, WD):
+    """Whether an FP32 plan of sub-array s (nearest cells g, compiled window size
+    WD) runs the paired-transform kernel: its grids, windows whose operands,
+    cell descriptors and samples fit a CU's 160 KB of LDS, and not dual pol at
+    N = 192 beyond 52 cells."""
+    N, P, K = s.grid_n, s.n_pol, s.kernel_k
+    if N not in (32, 48, 64, 96, 128, 192, 256) or (N == 192 and P == 2 and WD > 52):
+        return False
+    pitch = ((WD // 2) | 1) * 8
+    NK = N // (1 if N <= 64 else (2 if N <= 128 else 8))
+    lo = g.min(1)
+    R4 = -(-int((g[:, :, 1].max(1) - lo[:, 1]).max() + K) // 4) * 4
+    W = int((g[:, :, 0].max(1) - lo[:, 0]).max()) + K
+    cells = 0
+    for gc, lc in zip(g, lo):                                  # non-empty cells, the most of any channel
+        hit = np.zeros((R4, W), bool)
+        for dy in range(K):
+            for dx in range(K):
+                hit[gc[:, 1] - lc[1] + dy, gc[:, 0] - lc[0] + dx] = True
+        cells = max(cells, int(hit.sum()))
+    lds = [4 * (-(-g.shape[1] * P // 4) * 4), 8 * (-(-cells // 64) * 64), -(-P * R4 // 16) * 16 * pitch * 2,
+           P * (-(-NK // 16) * 16) * pitch * 2]
+    return sum(-(-b // 16) * 16 for b in lds) <= 160 * 1024
+
+
 def grid_mfma_per_call(info, subs, T):
     """MFMA 16x16x32 instructions of the gridding product of a GEMM-gridding
     plan: per column part and channel, each block entry is multiplied once per
-    step of grid_step spectra and per split term (FP16 2, FP8 3)."""
+    step of grid_step spectra and per split term (FP16 2, FP8 3).  Direct form:
+    every tile of 8 pixels by every block of 16 antennas, hi and lo, per step."""
     total = 0
     for k, s in enumerate(subs):
         if info["grid_form"][k] == 1:
+            continue
+        if info["grid_form"][k] == 4:
+            total += s.n_chan * (s.grid_n ** 2 // 8) * -(-s.n_ant // 16) * 2 * -(-T // info["grid_step"][k])
             continue
         terms = 3 if info["precision"] == 2 else 2
         steps = -(-T // info["grid_step"][k])
@@ -466,10 +499,18 @@ def main():
             + f", T={T} spectra per step", "n_time": T, "precision": precision,
             "plan": {k: info32[k] for k in ("batched", "can_batch", "form_ms", "autotuned", "graph", "weight",
                                             "slots", "lds_bytes", "grid_form", "grid_step")}},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / FP32_PEAK_TFLOPS, "traffic": counter_traffic(family, precision, wl.name),
-                     "kernel_ms": kern_ms, "algorithmic_flops_per_launch": flops_per_launch},
     }
+    # the matrix products that the kernel executes, against the dense FP16 peak
+    # (gridding products against their own type's), where it has any; the vector
+    # ALU otherwise.  What bounds the paired-transform kernel is the issue of both.
+    mfma = mfma_fraction(info32, kern_ms)
+    on_matrix_cores = mfma["executed_ops_per_call"] + mfma["grid_ops_per_call"] > 0
+    res["roofline"] = {"bound": "mfma" if on_matrix_cores else "alu",
+                       "achieved": mfma["executed_tflops"] + mfma["grid_tflops"] if on_matrix_cores else achieved,
+                       "peak": FP16_MFMA_PEAK_TFLOPS if on_matrix_cores else FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
+                       "frac": mfma["frac_total"] if on_matrix_cores else achieved / FP32_PEAK_TFLOPS,
+                       "algorithmic_tflops": achieved, "traffic": counter_traffic(family, precision, wl.name),
+                       "kernel_ms": kern_ms, "algorithmic_flops_per_launch": flops_per_launch}
     if res["roofline"]["traffic"] is not None:
         res["roofline"]["hbm_frac"] = res["roofline"]["traffic"] / (kern_ms * 1e-3) / (HBM_PEAK_GBS * 1e9)
     res["roofline"]["kernel_family"] = family
@@ -481,7 +522,7 @@ def main():
         res["roofline"]["executed_fp32"] = {"tflops": ex, "frac_of_peak": ex / FP32_PEAK_TFLOPS,
                                             "flops_per_launch": valu["fp_flops_per_launch"],
                                             "profile": valu["profile"]}
-    res["roofline"]["mfma"] = mfma_fraction(info32, kern_ms)
+    res["roofline"]["mfma"] = mfma
     par = {"reference": None if ref is None else
            f"FP64 oracle, all {subs[0].n_chan} channels x {T_par} spectra of sub-array 0"}
     par[f"{precision}:{args.gridder}"] = parity(img32, precision)

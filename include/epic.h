@@ -49,7 +49,9 @@ typedef enum {
 
 /* Arithmetic of the grid / transform stages.  Accumulation is always FP32. */
 typedef enum {
-    EPIC_FP32 = 0,   /* FP32 vector ALU: gather gridding + register FFT */
+    EPIC_FP32 = 0,   /* FP32 gather gridding and sums.  Transforms on the matrix cores, every
+                        operand an FP16 hi + lo pair (22 to 23 bits of it), or on the vector
+                        ALU where the shape has no such kernel and for electric fields */
     EPIC_FP16 = 1,   /* FP16 matrix cores (MFMA) for the transform stages; gridding as
                         the FP32 gather or as an FP16 product (hi + lo weights) */
     EPIC_FP8 = 2     /* gridding as an FP8 e4m3 product on the matrix cores (4-bit

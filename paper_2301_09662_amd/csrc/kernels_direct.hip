@@ -32,7 +32,7 @@ namespace {
 
 constexpr int kDirWaves = 4;       // waves per workgroup
 constexpr int kDirTilesPerWave = 2;   // 8-pixel tiles per wave
-constexpr int kDirSteps = 2;       // steps of spectra a workgroup takes at least
+constexpr int kDirSteps = 2;       // steps of spectra per workgroup in a call of max_time
 constexpr int kDirMaxBlk = 4;      // antenna blocks of 16 (A <= 64)
 
 struct DirArgs {
@@ -257,9 +257,11 @@ int dir_groups(const SubDev& d) {
 // Launch shape of the direct form: (channel, pixel group, time chunk)
 // workgroups of 4 waves, 16 pixels per wave; the chunks (one partial
 // accumulator slot each) bring the launch to at least ~8 workgroups per CU, but
-// each takes at least two steps of spectra: every workgroup reads its fragments
-// of M and writes its slot once, whatever it multiplies (48 antennas, 8 channels,
-// 100 spectra: 16.5 us a call at one step, 16.1 at two, 16.6 at four).
+// not past one per two steps of spectra in a call of max_time: every workgroup
+// reads its fragments of M and writes its slot once, whatever it multiplies (48
+// antennas, 8 channels, 100 spectra: 16.5 us a call at one step, 16.1 at two, 16.6
+// at four).  A shorter call keeps the plan's chunks, at most one per spectrum, so
+// its workgroups may take less than a step.
 // Arrays of at most 64 antennas on grids up to 64 whose X and Y weights are
 // equal (the fragments of M for 64 antennas fill 64 registers).
 hipError_t direct_configure(SubDev& d, int num_cu, int64_t max_time) {

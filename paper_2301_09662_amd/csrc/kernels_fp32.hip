@@ -1,9 +1,12 @@
 // FP32 path with the transforms on the vector ALU: the E-field images of every
 // FP32 plan, and the images of the grids and windows that the paired-transform
-// kernel does not hold (N = 16, 80, 112; windows of more than 64 cells).  For
+// kernel does not hold (N = 16, 80, 112; windows of more than 64 cells; dual pol
+// on N = 64 and 128 with a filled window of more than about 57 x 57 cells, whose
+// operands and descriptors exceed LDS; dual pol on N = 192 beyond 52 cells).  For
 // E-fields it stays ahead in accuracy, 1.3e-7 against 1.4e-7 from 64 bits, at
-// 30 against 28 us for 10 spectra of the 256-antenna station, where writing the
-// images bounds both.
+// 30 against 28 us for 33 channels x 40 spectra of the 256-antenna station.  (Its
+// E-field launch takes the occupancy of the image instance, two workgroups per
+// CU at N = 64: 2.6 rounds of spectra.)
 // One persistent fused kernel per sub-array.  Each workgroup
 // takes an equal, contiguous run of the (channel, spectrum) sequence and, for
 // each spectrum,

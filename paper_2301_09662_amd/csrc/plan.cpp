@@ -967,8 +967,8 @@ hipError_t launch_step(epic_plan_s* p, const uint8_t* const* d_samples, int64_t 
 // Replay the step from a captured hipGraph.  Each (spectra count, input
 // pointers, first call after a reset or not) gets its own executable graph;
 // the kGraphCache most recently used are kept, so a caller that rotates over
-// a few input buffers replays instead of capturing again.  A step of one kernel
-// is recorded without a graph and launched as it is: replaying a one-node graph
+// a few input buffers replays instead of capturing again.  A step of one image
+// kernel is recorded without a graph and launched as it is: replaying a one-node graph
 // takes longer than its launch (48 antennas imaged directly, 8 channels, 100
 // spectra: 40.5 us a call replayed, 16.5 us launched).
 constexpr size_t kGraphCache = 8;

@@ -50,13 +50,14 @@
 // them before they are decoded.  Eight waves of at most 128 registers (N = 64)
 // keep two workgroups on a CU.  Whole calls, against the kernels this one
 // replaced (vector-ALU transforms in FP32; one DFT row per image row in FP16):
-// station FP32 1099 -> 571 us, FP16 530 -> 430 us; 2048 antennas, N = 128, FP32
-// 2414 -> 1750 us; station on a 256 grid, FP32 2239 -> 1296 us.  With 2048
+// station FP32 1099 -> 568 us, FP16 530 -> 430 us; 2048 antennas, N = 128, FP32
+// 2414 -> 1690 us; station on a 256 grid, FP32 2239 -> 1285 us.  With 2048
 // antennas the gather's LDS reads and scattered writes bound it instead (1.06 of
 // 1.97 ms when each phase was left out in turn).  FP32 errors
-// against 64-bit images stay below those of the vector-ALU transforms (station
-// 1.6e-7 against 1.8e-7, 77 antennas at N = 48 0.6e-7 against 1.0e-7, 256 grid
-// 2.0e-7 against 2.2e-7).
+// against 64-bit images are below those of the vector-ALU transforms on arrays of
+// evenly weighted antennas (station 1.7e-7 against 1.8e-7, 77 antennas at N = 48
+// 0.6e-7 against 1.0e-7, 256 grid 2.0e-7 against 2.2e-7); for the others see
+// above.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

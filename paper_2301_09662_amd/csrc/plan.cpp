@@ -883,13 +883,37 @@ void set_tap_peaks(SubHost& h) {
             h.tap_peak[q] = std::max(h.tap_peak[q], std::fabs(h.user_taps[q * kk + k]) + std::fabs(h.user_taps[q * kk + k + 1]));
 }
 
+// The gains' sizes in one pass over their bits, which order like them: the
+// largest and the smallest non-zero larger component, and whether all are finite.
+struct GainSize {
+    bool finite = true;
+    float hi = 0.f, lo = 0.f;
+};
+GainSize gain_size(const float* gains, size_t n) {
+    uint32_t hi = 0, lo = ~0u;   // lo: less one, so that zero is the largest
+    for (size_t k = 0; k < n; ++k) {
+        uint32_t g[2];
+        std::memcpy(g, gains + 2 * k, sizeof(g));
+        const uint32_t m = std::max(g[0] & 0x7FFFFFFFu, g[1] & 0x7FFFFFFFu);
+        hi = std::max(hi, m);
+        lo = std::min(lo, m - 1);
+    }
+    ++lo;
+    GainSize s;
+    s.finite = hi < 0x7F800000u;
+    std::memcpy(&s.hi, &hi, sizeof(hi));
+    std::memcpy(&s.lo, &lo, sizeof(lo));
+    return s;
+}
+
 // Whether the antennas of some channel and pol weigh so differently that the
 // FP32 scales have to go by the samples: gains (null: 1) times tap peaks, zeros
 // left out.  The default Gaussians' own peaks are within a factor of four of
 // each other and are not counted.
-bool weights_uneven(const SubHost& h, const float* gains) {
+bool weights_uneven(const SubHost& h, const float* gains, const GainSize& size) {
     const int64_t A = h.desc.n_ant, P = h.desc.n_pol, C = h.desc.n_chan;
     if (!gains && h.tap_peak.empty()) return false;
+    if (h.tap_peak.empty() && (size.hi == 0.f || size.hi < 0.5f * kPairSpread * size.lo)) return false;   // even as a whole
     for (int64_t c = 0; c < C; ++c)
         for (int64_t p = 0; p < P; ++p) {
             float hi = 0.f, lo = std::numeric_limits<float>::infinity();
@@ -906,6 +930,7 @@ bool weights_uneven(const SubHost& h, const float* gains) {
 }
 
 bool capturing(hipStream_t st) {
+    if (!st) return false;   // the null stream cannot be captured
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
         (void)hipGetLastError();
@@ -1403,7 +1428,7 @@ epic_status make_plan(const epic_plan_desc* desc, hipStream_t st, epic_plan_s* p
         d.gains = nullptr;
         if (d.range) {
             set_tap_peaks(h);
-            h.uneven = weights_uneven(h, nullptr);
+            h.uneven = weights_uneven(h, nullptr, {});
         }
         const size_t nslot = (size_t)d.S * d.C * d.NPP * d.N * d.N;
         if ((s = dalloc(p, &d.slots, nslot)) != EPIC_OK) return s;
@@ -1681,9 +1706,10 @@ epic_status epic_set_gains(epic_plan_t p, int32_t sub, const float* h_gains, voi
     if (p->dry_run || p->sticky != EPIC_OK) return EPIC_E_STATE;
     SubDev& d = p->subs[sub].dev;
     const size_t n = (size_t)d.C * d.A * d.P * 2;
+    GainSize size;
     if (h_gains) {
-        for (size_t k = 0; k < n; ++k)
-            if (!std::isfinite(h_gains[k])) return EPIC_E_ARG;
+        size = gain_size(h_gains, n / 2);
+        if (!size.finite) return EPIC_E_ARG;
         // real weights take real gains; weights shared by both pols also need
         // equal X and Y gains (else the plan needs EPIC_F_COMPLEX_WEIGHTS)
         if (d.wmode != kWComplex)
@@ -1705,7 +1731,7 @@ epic_status epic_set_gains(epic_plan_t p, int32_t sub, const float* h_gains, voi
     if (!recorded) p->ac_pending[sub] = 0;
     if (d.range) {
         if (!p->gains_captured && capturing(st)) p->gains_captured = 1;
-        p->subs[sub].uneven = weights_uneven(p->subs[sub], h_gains);
+        p->subs[sub].uneven = weights_uneven(p->subs[sub], h_gains, size);
     }
     if (!h_gains) {
         d.gains = nullptr;

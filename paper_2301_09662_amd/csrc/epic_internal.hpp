@@ -113,7 +113,6 @@ struct SubDev {
     float* peak = nullptr;            // [C][A][P] largest |weight| of an antenna
     int32_t* row_top = nullptr;       // [C] most entries of a window row
     float* range = nullptr;           // [2][C][kRowBounds][P] the same by a call's samples too (accumulate, noalloc)
-    int32_t* uneven = nullptr;        // [2][C] 1: the channel's weights are uneven
     int use_range = 0;                // per call: the samples are looked through for that bound
     // gridding on the matrix cores (EPIC_GRID_DENSE_GEMM / EPIC_GRID_BLOCK_GEMM)
     int gridder = EPIC_GRID_GATHER;   // gridding form this sub-array's kernel runs

@@ -182,109 +182,92 @@ __global__ void __launch_bounds__(256) weights_kernel(GatherProgram plain, int n
 }
 
 // ---- the range of the gridded values (FP32 form) --------------------------
-// One block per channel: clears its bound and says whether the antennas of a pol
-// (those that weigh anything) differ by kPairSpread or more.
-template <int P>
-__global__ void __launch_bounds__(256) range_start_kernel(const float* __restrict__ peak, int A,
-                                                          float* __restrict__ range, int32_t* __restrict__ uneven) {
-    __shared__ float red[2][4][2];
-    const int c = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    float hi = 0.f, lo = __builtin_huge_valf();   // of the thread's pol: the block's size is even
-    for (int k = threadIdx.x; k < A * P; k += 256) {
-        const float w = peak[(int64_t)c * A * P + k];
-        if (w > 0.f) {
-            hi = fmaxf(hi, w);
-            lo = fminf(lo, w);
-        }
-    }
-    for (int m = 32; m >= P; m >>= 1) {
-        hi = fmaxf(hi, __shfl_xor(hi, m));
-        lo = fminf(lo, __shfl_xor(lo, m));
-    }
-    if (lane < P) {
-        red[lane][wv][0] = hi;
-        red[lane][wv][1] = lo;
-    }
-    __syncthreads();
-    if (threadIdx.x < P) range[(int64_t)c * kRowBounds * P + threadIdx.x] = 0.f;
-    if (threadIdx.x != 0) return;
-    int far = 0;
-    for (int p = 0; p < P; ++p) {
-        for (int w = 0; w < 4; ++w) {
-            hi = w ? fmaxf(hi, red[p][w][0]) : red[p][w][0];
-            lo = w ? fminf(lo, red[p][w][1]) : red[p][w][1];
-        }
-        if (hi > 0.f && !(hi < kPairSpread * lo)) far = 1;
-    }
-    uneven[c] = far;
-}
-
-// The largest product of an antenna's weight and a bound of its samples in
-// kRangeChunk spectra (blockIdx.x) of an uneven channel (blockIdx.y), times the
-// 2 row_top[c] components that a window row gathers at most.  A thread takes a
-// word of the row (four samples; a byte where rows are no aligned words) and ORs
-// the magnitudes of its nibbles over the spectra: at least the largest of them
-// and less than twice that.  Bound by reading the samples, eight words in flight
-// (station, 132 channels x 1000 spectra: 64 us a call at a byte and a maximum
-// per sample, 23 us by words).
-constexpr int kRangeChunk = 64;
+// A call's bounds of the window's rows, [C][kRowBounds][P] like the weights' own
+// (row_bound): those, where the antennas of a pol (the ones that weigh anything)
+// differ by less than kPairSpread; else bound b of a channel is what its b-th
+// share of the spectra can make of a row.  Block (share, channel).  A row gathers
+// at most 2 row_top[c] components, none above the largest product of an antenna's
+// weight and a bound of its samples: a thread takes a word of the samples' row
+// (four samples; a byte where rows are no aligned words) and ORs the magnitudes of
+// its nibbles over the spectra, at least the largest of them and less than twice
+// that.  Bound by reading the samples, eight words in flight (station, 132
+// channels x 1000 spectra: 64 us a call at a byte and a maximum per sample, 19 us
+// by words; where the weights are even, 4 us).
 template <int P, typename Word>
 __global__ void __launch_bounds__(256) range_kernel(const Word* __restrict__ samples, int64_t T, int C, int W,
                                                     const float* __restrict__ peak, const int32_t* __restrict__ row_top,
-                                                    const int32_t* __restrict__ uneven, float* __restrict__ range) {
-    const int c = blockIdx.y;
-    if (!uneven[c]) return;
+                                                    const float* __restrict__ row_bound, float* __restrict__ range) {
     constexpr int NS = sizeof(Word);   // samples per word
-    __shared__ float red[4][2];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t t0 = (int64_t)blockIdx.x * kRangeChunk, CW = (int64_t)C * W;
-    const int n = (int)(t0 + kRangeChunk < T ? kRangeChunk : T - t0);
+    __shared__ float red[4][2][2];
+    const int c = blockIdx.y, share = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const float* pk = peak + (int64_t)c * W * NS;
+    const float* rb = row_bound + (int64_t)c * kRowBounds * P;
+    float* out = range + ((int64_t)c * kRowBounds + share) * P;
+    {   // largest and smallest weight of the thread's pol (the block's size is even)
+        float hi = 0.f, lo = __builtin_huge_valf();
+#pragma unroll 8
+        for (int k = tid; k < W * NS; k += 256) {
+            const float w = pk[k];
+            hi = fmaxf(hi, w);
+            if (w > 0.f) lo = fminf(lo, w);
+        }
+        for (int x = 32; x >= P; x >>= 1) {
+            hi = fmaxf(hi, __shfl_xor(hi, x));
+            lo = fminf(lo, __shfl_xor(lo, x));
+        }
+        if (lane < P) {
+            red[wv][lane][0] = hi;
+            red[wv][lane][1] = lo;
+        }
+    }
+    __syncthreads();
+    bool far = false;
+    for (int p = 0; p < P; ++p) {
+        const float hi = fmaxf(fmaxf(red[0][p][0], red[1][p][0]), fmaxf(red[2][p][0], red[3][p][0]));
+        const float lo = fminf(fminf(red[0][p][1], red[1][p][1]), fminf(red[2][p][1], red[3][p][1]));
+        far = far || (hi > 0.f && !(hi < kPairSpread * lo));
+    }
+    if (!far) {
+        if (tid < P) out[tid] = rb[share * P + tid];
+        return;
+    }
+    const int64_t t0 = T * share / kRowBounds, n = T * (share + 1) / kRowBounds - t0, CW = (int64_t)C * W;
     // short rows: several thread groups take every so-manieth spectrum
-    const int groups = W < 256 ? 256 / W : 1, group = W < 256 ? threadIdx.x / W : 0;
+    const int groups = W < 256 ? 256 / W : 1, group = W < 256 ? tid / W : 0;
     float m[2] = {0.f, 0.f};
-    for (int k = threadIdx.x - group * W; group < groups && k < W; k += 256) {
+    for (int k = tid - group * W; group < groups && k < W; k += 256) {
         const Word* src = samples + (t0 * C + c) * W + k;
         uint32_t most = 0;
-#pragma unroll 8
-        for (int u = group; u < n; u += groups) {
-            const uint32_t x = src[u * CW], neg = (x >> 3) & 0x11111111u;
-            most |= (x ^ (neg * 15u)) + neg;   // nibble magnitudes, 0 to 8
+        for (int64_t u = group; u < n; u += 8 * groups) {
+            uint32_t x[8];   // past the end: the last spectrum again
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = src[(u + j * groups < n ? u + j * groups : n - 1) * CW];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t neg = (x[j] >> 3) & 0x11111111u;
+                most |= (x[j] ^ (neg * 15u)) + neg;   // nibble magnitudes, 0 to 8
+            }
         }
         most |= most >> 4;
 #pragma unroll
         for (int q = 0; q < NS; ++q) {
             const int s = k * NS + q, p = P == 2 ? (NS > 1 ? q & 1 : s & 1) : 0;
             const uint32_t size = (most >> (8 * q)) & 15u;
-            const float v = size ? (float)size * peak[((int64_t)c * W) * NS + s] : 0.f;
-            m[p] = fmaxf(m[p], v);
+            m[p] = fmaxf(m[p], size ? (float)size * pk[s] : 0.f);
         }
     }
+    __syncthreads();   // red has been read
 #pragma unroll
-    for (int p = 0; p < P; ++p)
+    for (int p = 0; p < P; ++p) {
         for (int x = 32; x > 0; x >>= 1) m[p] = fmaxf(m[p], __shfl_xor(m[p], x));
-    if (lane == 0)
-        for (int p = 0; p < P; ++p) red[wv][p] = m[p];
+        if (lane == 0) red[wv][p][0] = m[p];
+    }
     __syncthreads();
-    if (threadIdx.x >= P) return;
-    const int p = threadIdx.x;
-    const float r = fmaxf(fmaxf(red[0][p], red[1][p]), fmaxf(red[2][p], red[3][p]));
-    // as integers: they order like the values
-    atomicMax(reinterpret_cast<unsigned int*>(range) + (int64_t)c * kRowBounds * P + p,
-              __float_as_uint(2.0f * (float)row_top[c] * r));
-}
-
-// The smaller bound of each channel and pol: the samples' (0: none), or the
-// largest of the rows' by the weights alone.
-__global__ void range_end_kernel(const float* __restrict__ row_bound, int C, int P, float* __restrict__ range) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= C * P) return;
-    const int64_t c = k / P, p = k - c * P;
-    const float* in = row_bound + c * kRowBounds * P + p;
-    float* out = range + c * kRowBounds * P + p;
-    float m = 0.f;
-    for (int r = 0; r < kRowBounds; ++r) m = fmaxf(m, in[r * P]);
-    out[0] = out[0] > 0.f ? fminf(m, out[0]) : m;
-    for (int r = 1; r < kRowBounds; ++r) out[r * P] = 0.f;
+    if (tid >= P) return;
+    const float r = fmaxf(fmaxf(red[0][tid][0], red[1][tid][0]), fmaxf(red[2][tid][0], red[3][tid][0]));
+    float rows = 0.f;   // what the weights alone allow
+    for (int k = 0; k < kRowBounds; ++k) rows = fmaxf(rows, rb[k * P + tid]);
+    out[tid] = fminf(rows, 2.0f * (float)row_top[c] * r);
 }
 
 // ---- autocorrelations (the a = b terms of Eq. 3) ---------------------------
@@ -744,23 +727,15 @@ hipError_t launch_weights(const SubDev& d, hipStream_t st) {
 
 hipError_t launch_range(const SubDev& d, const uint8_t* samples, int64_t n_time, hipStream_t st) {
     const int AP = d.A * d.P;
-    const dim3 grid((unsigned)((n_time + kRangeChunk - 1) / kRangeChunk), d.C), block(256);
-    const bool words = (AP & 3) == 0 && (reinterpret_cast<uintptr_t>(samples) & 3) == 0;
-#define EPIC_RANGE(PP)                                                                                              \
-    range_start_kernel<PP><<<dim3(d.C), block, 0, st>>>(d.peak, d.A, d.range, d.uneven);                           \
-    if (words)                                                                                                      \
-        range_kernel<PP, uint32_t><<<grid, block, 0, st>>>(reinterpret_cast<const uint32_t*>(samples), n_time, d.C, \
-                                                           AP / 4, d.peak, d.row_top, d.uneven, d.range);           \
-    else                                                                                                            \
-        range_kernel<PP, uint8_t><<<grid, block, 0, st>>>(samples, n_time, d.C, AP, d.peak, d.row_top, d.uneven,    \
-                                                          d.range)
-    if (d.P == 2) {
-        EPIC_RANGE(2);
+    const dim3 grid(kRowBounds, d.C), block(256);
+    if ((AP & 3) == 0 && (reinterpret_cast<uintptr_t>(samples) & 3) == 0) {
+        const auto fn = d.P == 2 ? range_kernel<2, uint32_t> : range_kernel<1, uint32_t>;
+        fn<<<grid, block, 0, st>>>(reinterpret_cast<const uint32_t*>(samples), n_time, d.C, AP / 4, d.peak, d.row_top,
+                                   d.row_bound, d.range);
     } else {
-        EPIC_RANGE(1);
+        const auto fn = d.P == 2 ? range_kernel<2, uint8_t> : range_kernel<1, uint8_t>;
+        fn<<<grid, block, 0, st>>>(samples, n_time, d.C, AP, d.peak, d.row_top, d.row_bound, d.range);
     }
-#undef EPIC_RANGE
-    range_end_kernel<<<dim3((d.C * d.P + 255) / 256), block, 0, st>>>(d.row_bound, d.C, d.P, d.range);
     return hipGetLastError();
 }
 

@@ -589,7 +589,6 @@ Tables list_tables(const epic_plan_s* p, SubHost& h, Arena& ar) {
             ar.add(&d.row_bound, (size_t)d.C * kRowBounds * d.P);
             ar.add(&d.peak, (size_t)d.C * d.A * d.P);
             ar.add(&d.range, (size_t)2 * d.C * kRowBounds * d.P);
-            ar.add(&d.uneven, (size_t)2 * d.C);
         }
     }
     if (t.direct) ar.put(&d.dir_m, (size_t)direct_matrix_halfs(d) * sizeof(uint16_t), nullptr);
@@ -949,8 +948,8 @@ bool captures_autocorr(epic_plan_s* p, hipStream_t st) {
 
 // The sub-arrays (bits) whose FP32 scales go by the samples in this call: those
 // with uneven weights.  What the caller captures is replayed under gains not
-// known here, so it holds the look at the samples in any case; its kernels
-// leave the channels with even weights alone.
+// known here, so it holds the look at the samples in any case; its kernel
+// leaves the channels with even weights alone.
 uint32_t ranged_subs(const epic_plan_s* p, hipStream_t st) {
     uint32_t bits = 0, pairs = 0;
     for (size_t k = 0; k < p->subs.size(); ++k) {
@@ -1687,10 +1686,8 @@ epic_status epic_image_noalloc(epic_plan_t p, const uint8_t* const* d_samples, i
         run[k].slots = base + off[k];
         run[k].fresh = 1;   // every slot that the read-out sums is stored by this call
         run[k].use_range = (ranged >> k) & 1;
-        if (run[k].use_range) {   // this call's own: an accumulate call may run on another stream
+        if (run[k].use_range)   // this call's own: an accumulate call may run on another stream
             run[k].range += (size_t)run[k].C * kRowBounds * run[k].P;
-            run[k].uneven += run[k].C;
-        }
     }
     for (size_t k = 0; k < run.size() && e == hipSuccess && n_time > 0; ++k) {
         const SubDev& d = run[k];

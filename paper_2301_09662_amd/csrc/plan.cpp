@@ -12,7 +12,6 @@
 #include <limits>
 #include <mutex>
 #include <new>
-#include <numeric>
 #include <set>
 #include <string>
 #include <vector>
@@ -236,17 +235,22 @@ void build_gather(SubHost& h) {
     h.cells_desc.clear(); h.grp_ant.clear(); h.grp_tap.clear();
     int Gmax = 0, CellMax = 0, SlicedMax = 0;
     std::vector<int> count, order, at, hist;   // per window cell: entries, then the next entry's place
+    std::vector<int> row_count;                // per window row: entries
     for (int c = 0; c < C; ++c) {
         ChanInfo& ci = h.chans[c];
         const int32_t* cc = &h.cells[(size_t)c * A * 2];
         const int n = ci.R * ci.W;
         count.assign(n, 0);
+        row_count.assign(ci.R, 0);
         int most = 0;
         for (int a = 0; a < A; ++a)
             for (int dy = 0; dy < K; ++dy) {
-                int* row = &count[(size_t)(cc[2 * a + 1] - hk + dy - ci.y0) * ci.W + cc[2 * a] - hk - ci.x0];
+                const int r = cc[2 * a + 1] - hk + dy - ci.y0;
+                row_count[r] += K;
+                int* row = &count[(size_t)r * ci.W + cc[2 * a] - hk - ci.x0];
                 for (int dx = 0; dx < K; ++dx) most = std::max(most, ++row[dx]);
             }
+        h.row_top[c] = *std::max_element(row_count.begin(), row_count.end());
         // non-empty cells by descending entry count, in raster order among equals
         hist.assign(most + 2, 0);
         for (int k = 0; k < n; ++k) ++hist[most - count[k] + 1];
@@ -280,8 +284,6 @@ void build_gather(SubHost& h) {
                     h.grp_tap[e] = (uint8_t)(dy * K + dx);
                 }
             }
-        for (int r = 0; r < ci.R; ++r)
-            h.row_top[c] = std::max(h.row_top[c], std::accumulate(&count[(size_t)r * ci.W], &count[(size_t)r * ci.W] + ci.W, 0));
         ci.n_grp = (int32_t)g;
         Gmax = std::max(Gmax, ci.n_grp);
         CellMax = std::max(CellMax, ci.n_cell);
